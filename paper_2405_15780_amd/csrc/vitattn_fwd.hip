@@ -42,7 +42,6 @@
 // running max m is kept pre-multiplied by the scale (m = fl(max * c)) and
 // subtracted inside one FMA, exp2(fma(s, c, -m)), so the largest P is 1 up
 // to the rounding of that product (one fp32 ulp of the scaled logit).
-#include <atomic>
 #include <type_traits>
 
 #include "vitattn_common.h"
@@ -341,7 +340,8 @@ static hipError_t launch_fwd_v(const FwdArgs& a) {
 // host-side launch stub of some instantiations reached only through this
 // dispatch, and the library then fails to load.
 #define VITATTN_FWD_VARIANTS(X) \
-  X(128, 2, 8, 2, 8) X(64, 2, 8, 2, 4) X(64, 2, 12, 3, 4) X(96, 2, 8, 2, 6) X(96, 2, 8, 2, 5) X(160, 1, 8, 2, 10)
+  X(128, 2, 8, 2, 8) X(64, 2, 8, 2, 4) X(64, 2, 12, 3, 4) X(96, 2, 8, 2, 6) X(96, 2, 8, 2, 5) X(160, 1, 8, 2, 10) \
+  X(128, 2, 4, 2, 8) X(64, 2, 4, 3, 4) X(96, 2, 4, 2, 6) X(96, 2, 4, 2, 5) X(160, 1, 4, 2, 10)
 #define VITATTN_FWD_INSTANTIATE(D, KB, NW, MINW, KS)                                                           \
   template __global__ void attn_fwd_kernel<D, KB, NW, MINW, KS>(                                              \
       const uint16_t* __restrict__, const uint16_t* __restrict__, const uint16_t* __restrict__,               \
@@ -350,53 +350,47 @@ static hipError_t launch_fwd_v(const FwdArgs& a) {
 VITATTN_FWD_VARIANTS(VITATTN_FWD_INSTANTIATE)
 #undef VITATTN_FWD_INSTANTIATE
 
-// Workgroups of a forward variant resident on the current device at once (0
-// if the runtime cannot say), looked up once per device.
-template <int D, int KB, int NW, int MINW>
-static int fwd_resident_workgroups() {
-  static std::atomic<int> known[64];
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;
-  int n = known[dev].load(std::memory_order_relaxed);
-  if (n == 0) {
-    int per_cu = 0, cus = 0;
-    n = -1;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, attn_fwd_kernel<D, KB, NW, MINW>, 64 * NW, 0) ==
-            hipSuccess &&
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && per_cu * cus > 0)
-      n = per_cu * cus;
-    known[dev].store(n, std::memory_order_relaxed);
+// Workgroups of a forward variant resident on the current device at once and
+// its CUs (zeros if the runtime cannot say), looked up once per device.
+template <int D, int KB, int NW, int MINW, int KS>
+static Resident fwd_resident() {
+  static ResidentCache cache;
+  return cache.get(reinterpret_cast<const void*>(attn_fwd_kernel<D, KB, NW, MINW, KS>), 64 * NW);
+}
+
+// Waves per workgroup, by the shorter estimated time (launch_cost below). A
+// workgroup of 4 waves (128 queries) has a CU's SIMDs to itself while the
+// grid leaves others idle: one alone on a CU takes 0.72-0.83 of the time of
+// 8 waves on it, two 1.02-1.05, three (d <= 64) 1.48 (measured at N = 16,384,
+// H = 1 .. 16, every width), so grids up to one per CU and those with a
+// nearly empty last round take it: B=1, H=1, N=1,024, d=64 20.3 -> 15.1 us,
+// B=1, H=2, N=16,384, d=128 334 -> 277 us. At the narrowest tile the kernel's
+// ~160 VGPRs fit three waves per SIMD: 12 waves (384 queries) share each K /
+// V tile, ~5 % faster per query than 8 (N = 188,416 and 1,048,576), but in
+// coarser work items. Each query row is computed by the same operations in
+// the same order in all of them, so the choice changes no bit.
+template <int D, int KB, int KS>
+static hipError_t launch_fwd_d(const FwdArgs& a) {
+  constexpr int MINW4 = D == 64 ? 3 : 2;
+  const Resident r8 = fwd_resident<D, KB, 8, 2, KS>(), r4 = fwd_resident<D, KB, 4, MINW4, KS>();
+  const double c8 = launch_cost(a.BH, a.Nq, 8, r8), c4 = launch_cost(a.BH, a.Nq, 4, r4);
+  if constexpr (D == 64) {
+    const double c12 = launch_cost(a.BH, a.Nq, 12, fwd_resident<D, KB, 12, 3, KS>()) / 1.05;
+    if (c12 < c8 && c12 < c4) return launch_fwd_v<D, KB, 12, 3, KS>(a);
   }
-  return n > 0 ? n : 0;
+  return c4 < c8 ? launch_fwd_v<D, KB, 4, MINW4, KS>(a) : launch_fwd_v<D, KB, 8, 2, KS>(a);
 }
 
-// At the narrowest tile the kernel's ~160 VGPRs fit three waves per SIMD: 12
-// waves (384 queries) per workgroup share each K / V tile and hide more of
-// the exponentials, ~4-6 % faster per query than 8 waves (measured at N =
-// 188,416 and 1,048,576), but in coarser work items. The variant with the
-// shorter estimated time (whole rounds of resident workgroups x queries per
-// workgroup / that rate) is launched; each query row is computed by the
-// same operations in the same order either way, so the choice changes no bit.
-static hipError_t launch_fwd_64(const FwdArgs& a) {
-  const int s8 = fwd_resident_workgroups<64, 2, 8, 2>(), s12 = fwd_resident_workgroups<64, 2, 12, 3>();
-  if (s8 <= 0 || s12 <= 0) return launch_fwd_v<64, 2, 8, 2>(a);
-  const long long t8 = (long long)a.BH * ((a.Nq + 255) / 256), t12 = (long long)a.BH * ((a.Nq + 383) / 384);
-  const double c8 = (double)((t8 + s8 - 1) / s8) * 8.0, c12 = (double)((t12 + s12 - 1) / s12) * 12.0 / 1.05;
-  return c12 < c8 ? launch_fwd_v<64, 2, 12, 3>(a) : launch_fwd_v<64, 2, 8, 2>(a);
-}
-
-// Tile shape per width (key blocks per tile, waves per workgroup, waves per
-// SIMD): two 32-key blocks per tile and 8 waves x 32 queries, except at
-// D = 160, where one key block per tile keeps the registers within budget,
-// and at D = 64, where 12 waves are chosen when the grid allows (above). In
-// the 96-wide tile a head dim up to 80 (ViT-10B's 72) contracts the scores
-// over five 16-column steps instead of six.
+// Tile shape per width: two 32-key blocks per tile, except at D = 160, where
+// one key block per tile keeps the registers within budget. In the 96-wide
+// tile a head dim up to 80 (ViT-10B's 72) contracts the scores over five
+// 16-column steps instead of six.
 hipError_t launch_fwd(const FwdArgs& a) {
   switch (tile_width(a.d)) {
-    case 64: return launch_fwd_64(a);
-    case 96: return a.d <= 80 ? launch_fwd_v<96, 2, 8, 2, 5>(a) : launch_fwd_v<96, 2, 8, 2>(a);
-    case 128: return launch_fwd_v<128, 2, 8, 2>(a);
-    default: return launch_fwd_v<160, 1, 8, 2>(a);
+    case 64: return launch_fwd_d<64, 2, 4>(a);
+    case 96: return a.d <= 80 ? launch_fwd_d<96, 2, 5>(a) : launch_fwd_d<96, 2, 6>(a);
+    case 128: return launch_fwd_d<128, 2, 8>(a);
+    default: return launch_fwd_d<160, 1, 10>(a);
   }
 }
 

@@ -4,7 +4,53 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
+
 namespace vitattn {
+
+// Workgroups of a kernel that the current device holds at once, and its CUs;
+// zeros if the runtime cannot say. Looked up once per device (no stream work,
+// so a graph capture may hold it).
+struct Resident {
+  int workgroups, cus;
+};
+class ResidentCache {
+ public:
+  Resident get(const void* kernel, int threads) {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kDevices) return {0, 0};
+    long long known = known_[dev].load(std::memory_order_relaxed);
+    if (known == 0) {
+      int per_cu = 0, cus = 0;
+      known = -1;
+      if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) == hipSuccess &&
+          hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && per_cu * cus > 0)
+        known = (long long)cus << 32 | (per_cu * cus);
+      known_[dev].store(known, std::memory_order_relaxed);
+    }
+    return known > 0 ? Resident{(int)(known & 0x7fffffff), (int)(known >> 32)} : Resident{0, 0};
+  }
+
+ private:
+  static constexpr int kDevices = 64;
+  std::atomic<long long> known_[kDevices] = {};  // 0 = not looked up, -1 = unknown
+};
+
+// Estimated time of a forward or dQ launch of `nw` waves (32 nw query rows)
+// per workgroup, in units of one round of 8-wave workgroups, one per CU:
+// whole rounds, then the last one by how many workgroups a CU gets. Only
+// 4-wave workgroups are ever resident in numbers on a CU. Without the
+// device's figures 8 waves win.
+inline double launch_cost(int BH, int Nq, int nw, const Resident& r) {
+  if (r.workgroups <= 0) return nw == 8 ? 0. : 1.;
+  const long long n = (long long)BH * ((Nq + 32 * nw - 1) / (32 * nw));
+  const long long rounds = n / r.workgroups, left = n - rounds * r.workgroups;
+  if (nw != 4) return (double)(rounds + (left > 0)) * (nw / 8.);
+  constexpr double of[4] = {0., 0.86, 1.04, 1.5};  // 1 .. 3 per CU: measured 0.66-0.86, 1.02-1.05, 1.48-1.52
+  const int per_cu = r.workgroups / r.cus < 3 ? r.workgroups / r.cus : 3;
+  const int last = (int)((left + r.cus - 1) / r.cus);
+  return rounds * of[per_cu] + of[last < per_cu ? last : per_cu];
+}
 
 // Where the rows of one [B][H][N][d] operand live: element strides of the
 // batch, head and row dimensions (the d elements of a row are contiguous).

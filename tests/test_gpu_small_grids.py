@@ -1,0 +1,43 @@
+"""Grids that leave CUs idle take narrower workgroups (the forward and dQ: four
+waves, 128 queries). One call over 200 heads of 200 tokens fills the chip and
+takes the eight-wave kernels; a single head of it takes the narrow ones. Every
+output must be bitwise equal between the two, and single calls at the edges of
+the narrow tiles must match the fp64 oracle."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+from gpu_util import assert_close, run_hip, torch
+
+pytestmark = pytest.mark.gpu
+
+
+def np64(t):
+    return t.detach().double().cpu().numpy()
+
+
+@pytest.mark.parametrize("store_ds", [False, True])
+@pytest.mark.parametrize("d", [64, 72, 96, 128, 160])
+def test_single_heads_equal_the_full_grid(d, store_ds):
+    t = torch()
+    B, H, N = 1, 200, 200
+    print(f"case small grids H={H} N={N} d={d} store_ds={store_ds}", flush=True)
+    x = workloads.make_small_inputs(B, H, N, d, seed=6100 + d)
+    scale = 1.0 / np.sqrt(d)
+    full = run_hip(x, scale, store_ds=store_ds)
+    for h in (0, 77, 199):
+        one = run_hip({n: np.ascontiguousarray(a[:, h:h + 1]) for n, a in x.items()}, scale, store_ds=store_ds)
+        for name in ("o", "lse", "dq", "dk", "dv"):
+            assert t.equal(full[name][:, h:h + 1], one[name]), (name, h)
+
+
+@pytest.mark.parametrize("N", [1, 31, 97, 127, 128, 129, 255, 385])
+@pytest.mark.parametrize("d", [40, 72, 88, 128, 160])
+def test_tile_edges_against_the_oracle(d, N):
+    print(f"case small grids, tile edges N={N} d={d}", flush=True)
+    x = workloads.make_small_inputs(1, 2, N, d, seed=6200 + N + d)
+    scale = 1.0 / np.sqrt(d)
+    got = {n: np64(a) for n, a in run_hip(x, scale).items()}
+    ref = oracle.forward_backward(x["q"], x["k"], x["v"], x["dout"], scale)
+    assert_close(got, ref, label=f"small grids N={N} d={d}")
