@@ -9,9 +9,9 @@
 //      queries:
 //        S = Q K^T, P = exp2(S*scale*log2e - LSE*log2e)
 //        dV^T += dO^T P,  dP = dO V^T,  dS = P o (dP - D),  dK^T += Q^T dS
-//   3. dQ kernel: one workgroup per 256 queries (or 384 at head dims up to 80;
-//      32 per wave, Q and dO held in registers); streams K and V in tiles of
-//      32 keys:
+//   3. dQ kernel: one workgroup per 256 queries (128 on small grids, 384 at
+//      head dims up to 80 on large ones; 32 per wave, Q and dO held in
+//      registers); streams K and V in tiles of 32 keys:
 //        S^T = K Q^T, P^T, dP^T = V dO^T, dS^T, dQ^T += K^T dS^T
 // Splitting dQ from dK/dV costs one extra recomputation of S and dP but needs
 // no atomics for dQ (accumulating dQ inside the dK/dV pass would add a 4-byte
@@ -23,7 +23,6 @@
 // grid. As in the forward pass, operands may have any batch / head / row
 // strides, and a head dim d below the tile width D is padded with zero
 // columns on load and cut off on store.
-#include <atomic>
 #include <type_traits>
 
 #include "vitattn_common.h"
@@ -645,7 +644,7 @@ __global__ __launch_bounds__(256) void zero_key_blocks_kernel(float* __restrict_
 // K_row^T dS = 0 to dQ, so no masking is needed. S and dP contract over the
 // KS 16-column steps of d that hold data (D/16, or 5 for d <= 80 in the
 // 96-wide tile).
-template <int D, int NW, int KS = D / 16>
+template <int D, int NW, int KS>
 __global__ __launch_bounds__(64 * NW, NW / 4) __attribute__((amdgpu_waves_per_eu(NW / 4, NW / 4))) void attn_bwd_dq_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const uint16_t* __restrict__ dout, const float* __restrict__ drow, const float* __restrict__ lse2,
@@ -655,6 +654,17 @@ __global__ __launch_bounds__(64 * NW, NW / 4) __attribute__((amdgpu_waves_per_eu
   constexpr int BN = 32;
   constexpr int KK = D / 16, NCB = D / 32;
   static_assert(KS >= 1 && KS <= KK, "contraction steps within the tile");
+  // LDS operands are read AH ops ahead: two, where one op (32 cycles) does not
+  // cover the read (8 waves: d=128 2,519 -> 2,419 us at H=16, N=16,384, d=160
+  // 3,156 -> 3,034, d=72 1,769 -> 1,702; 4 waves: 374 -> 270 us at H=1, d=128;
+  // three measured the same as two). The 12-wave form at D = 96 would spill
+  // in the loop (28.8 -> 32.8 ms at H=2, N=188,416, d=72) and keeps one.
+  constexpr int AH = D == 96 && NW == 12 ? 1 : 2;
+  // At the narrowest tile, where the vector work outweighs the matrix cores',
+  // an op's slice of it goes before the op, while the op's operand is still
+  // on its way (3 % faster at H=1, N=16,384, 1 % at full grids; no change at
+  // the wider tiles, and spills at D = 160).
+  constexpr bool ROWS_FIRST = D == 64;
   constexpr int NS = 2 * KS;       // S and dP ops per tile
   constexpr int NQ = KK;           // dQ ops per tile (2 contraction steps x NCB)
   constexpr int TILE_BYTES = BN * D * 2;
@@ -757,7 +767,7 @@ __global__ __launch_bounds__(64 * NW, NW / 4) __attribute__((amdgpu_waves_per_eu
     };
     if constexpr (NEXT) {
       // One stream of NS score ops (tile j+1) then NQ dQ ops (tile j), each
-      // operand read one op ahead; row r of the vector work rides on op
+      // operand read AH ops ahead; row r of the vector work rides on op
       // r*W/16, so dS rows 8..15 are complete two ops before the dQ op that
       // first reads them.
       constexpr int NOPS = NS + NQ;
@@ -769,8 +779,15 @@ __global__ __launch_bounds__(64 * NW, NW / 4) __attribute__((amdgpu_waves_per_eu
         const int t = i - NS;
         return tf.load(ks, 16 * (t / NCB), t % NCB);
       };
-      bf16x8 aq[2];
-      aq[0] = load_op(0);
+      auto rows = [&](auto IC) __attribute__((always_inline)) {
+        static_for<0, 16>([&](auto RC) __attribute__((always_inline)) {
+          constexpr int r = decltype(RC)::value;
+          if constexpr (r * W / 16 == decltype(IC)::value) row(r);
+        });
+      };
+      bf16x8 aq[AH + 1];
+#pragma unroll
+      for (int i = 0; i < AH; ++i) aq[i] = load_op(i);
       sched_fence();
       static_for<0, NOPS>([&](auto IC) __attribute__((always_inline)) {
         constexpr int i = decltype(IC)::value;
@@ -782,23 +799,21 @@ __global__ __launch_bounds__(64 * NW, NW / 4) __attribute__((amdgpu_waves_per_eu
         if constexpr (i == 0) __builtin_amdgcn_s_setprio(NW > 8 ? 2 : 1);
         if constexpr (NW > 8 && i == W / 2) __builtin_amdgcn_s_setprio(1);
         if constexpr (i == W) __builtin_amdgcn_s_setprio(0);
-        if constexpr (i + 1 < NOPS) aq[(i + 1) & 1] = load_op(i + 1);
+        if constexpr (i + AH < NOPS) aq[(i + AH) % (AH + 1)] = load_op(i + AH);
+        if constexpr (ROWS_FIRST) rows(IC);
         if constexpr (i < NS) {
           if constexpr (i % KS == 0) nxt[i / KS] = zero16();
           if constexpr (i < KS)
-            nxt[0] = mfma32(aq[i & 1], qf[i], nxt[0]);
+            nxt[0] = mfma32(aq[i % (AH + 1)], qf[i], nxt[0]);
           else
-            nxt[1] = mfma32(aq[i & 1], gf[i - KS], nxt[1]);
+            nxt[1] = mfma32(aq[i % (AH + 1)], gf[i - KS], nxt[1]);
         } else {
           constexpr int t = i - NS;
-          dqacc[t % NCB] = mfma32(aq[i & 1], dsb[t / NCB], dqacc[t % NCB]);
+          dqacc[t % NCB] = mfma32(aq[i % (AH + 1)], dsb[t / NCB], dqacc[t % NCB]);
         }
         if constexpr (i == 1) dma.issue(rk, (j + 4) * BN, ldk, kbuf[RF]);
         if constexpr (i == 3) dmv.issue(rv, (j + 4) * BN, ldv, vbuf[RF]);
-        static_for<0, 16>([&](auto RC) __attribute__((always_inline)) {
-          constexpr int r = decltype(RC)::value;
-          if constexpr (r * W / 16 == i) row(r);
-        });
+        if constexpr (!ROWS_FIRST) rows(IC);
         sched_fence();
       });
       if constexpr ((SL & 1) == 1) {
@@ -1055,24 +1070,11 @@ static hipError_t rowdot_l(const BwdArgs& a) {
   return hipGetLastError();
 }
 
-// Workgroups of the dK/dV kernel resident on the current device at once
-// (0 if the runtime cannot say), looked up once per device.
+// Workgroups of the dK/dV kernel resident on the current device at once.
 template <int D, bool STORE_DS, int KBW, int KPW, int KS>
-static int dkdv_resident_workgroups() {
-  static std::atomic<int> known[64];  // per device ordinal; 0 = not looked up, -1 = unknown
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;
-  int n = known[dev].load(std::memory_order_relaxed);
-  if (n == 0) {
-    int per_cu = 0, cus = 0;
-    n = -1;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, attn_bwd_dkdv_kernel<D, STORE_DS, KBW, KPW, KS>,
-                                                     128 * KBW, 0) == hipSuccess &&
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && per_cu * cus > 0)
-      n = per_cu * cus;
-    known[dev].store(n, std::memory_order_relaxed);
-  }
-  return n > 0 ? n : 0;
+static Resident dkdv_resident() {
+  static ResidentCache cache;
+  return cache.get(reinterpret_cast<const void*>(attn_bwd_dkdv_kernel<D, STORE_DS, KBW, KPW, KS>), 128 * KBW);
 }
 
 template <int D, bool STORE_DS, int KBW, int KPW, int KS = D / 16>
@@ -1082,7 +1084,7 @@ static hipError_t dkdv_s(const BwdArgs& a) {
   const int total = a.BH * n_kt;
   // A last round at most half full is split in two halves of the query range
   // (when there are two query tiles to split), so that it takes half as long.
-  const int slots = dkdv_resident_workgroups<D, STORE_DS, KBW, KPW, KS>();
+  const int slots = dkdv_resident<D, STORE_DS, KBW, KPW, KS>().workgroups;
   const int tail = slots > 0 ? total % slots : 0;
   int n_whole = total;
   if (tail > 0 && 2 * tail <= slots && (a.Nq + kDkvBQ - 1) / kDkvBQ >= 2) {
@@ -1162,7 +1164,7 @@ VITATTN_DQDS_INSTANTIATE(128, 8, 6)
 VITATTN_DQDS_INSTANTIATE(160, 8, 6)
 #undef VITATTN_DQDS_INSTANTIATE
 
-template <int D, int NW, int KS = D / 16>
+template <int D, int NW, int KS>
 static hipError_t dq_v(const BwdArgs& a) {
   const int n_qt = (a.Nq + 32 * NW - 1) / (32 * NW);
   const int total = a.BH * n_qt;
@@ -1178,12 +1180,17 @@ static hipError_t dq_v(const BwdArgs& a) {
       const uint16_t* __restrict__, const float* __restrict__, const float* __restrict__, float* __restrict__, \
       const Map, const Map, const Map, const Map, const Map, int, int, int, int, int, int, float, float, int);
 VITATTN_DQ_INSTANTIATE(128, 8, 8)
+VITATTN_DQ_INSTANTIATE(128, 4, 8)
 VITATTN_DQ_INSTANTIATE(64, 8, 4)
+VITATTN_DQ_INSTANTIATE(64, 4, 4)
 VITATTN_DQ_INSTANTIATE(64, 12, 4)
 VITATTN_DQ_INSTANTIATE(96, 8, 6)
+VITATTN_DQ_INSTANTIATE(96, 4, 6)
 VITATTN_DQ_INSTANTIATE(96, 8, 5)
+VITATTN_DQ_INSTANTIATE(96, 4, 5)
 VITATTN_DQ_INSTANTIATE(96, 12, 5)
 VITATTN_DQ_INSTANTIATE(160, 8, 10)
+VITATTN_DQ_INSTANTIATE(160, 4, 10)
 #undef VITATTN_DQ_INSTANTIATE
 
 hipError_t launch_bwd_rowdot(const BwdArgs& a) {
@@ -1206,51 +1213,40 @@ hipError_t launch_bwd_dq_ds(const BwdArgs& a) {
     default: return dq_ds_d<160>(a);
   }
 }
-// Workgroups of a dQ kernel variant resident on the current device at once
-// (0 if the runtime cannot say), looked up once per device.
+// Workgroups of a dQ kernel variant resident on the current device at once.
 template <int D, int NW, int KS>
-static int dq_resident_workgroups() {
-  static std::atomic<int> known[64];
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;
-  int n = known[dev].load(std::memory_order_relaxed);
-  if (n == 0) {
-    int per_cu = 0, cus = 0;
-    n = -1;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, attn_bwd_dq_kernel<D, NW, KS>, 64 * NW, 0) == hipSuccess &&
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && per_cu * cus > 0)
-      n = per_cu * cus;
-    known[dev].store(n, std::memory_order_relaxed);
-  }
-  return n > 0 ? n : 0;
+static Resident dq_resident() {
+  static ResidentCache cache;
+  return cache.get(reinterpret_cast<const void*>(attn_bwd_dq_kernel<D, NW, KS>), 64 * NW);
 }
 
-// At the narrowest tile (168 VGPRs, three values spilled and reloaded only
-// after the tile loop) and at D = 96 with five contraction steps (168, one
-// 16-byte operand spilled and reloaded three times per six tiles) the dQ
-// kernel fits three waves per SIMD: 12 waves (384 queries) per workgroup share
-// each K / V tile, faster per query than 8 waves (~6 % at D = 64, B=4, H=1, N=188,416;
-// ~4.5 % at d = 72, B=1, H=2-3, N=50,001-188,416), but in coarser work items.
-// The variant with the shorter estimated time (whole rounds of resident
-// workgroups x queries per workgroup / that rate) is launched; both compute
-// every dQ row with the same operations in the same order, so the choice
-// changes no bit.
+// Waves per workgroup, by the shorter estimated time (launch_cost). Four
+// waves, one per SIMD, take 0.66-0.86 of the time of eight on a CU, so grids
+// that leave CUs idle with 256 queries per workgroup take them (B=1, H=2,
+// N=16,384, d=128: 400 -> 345 us; N=4,096: 119 -> 75 us). At d <= 80 the kernel fits
+// three waves per SIMD (three to five values spilled, outside the loop but for
+// one operand at D = 96): 12 waves (384 queries) share each K / V tile, 2 %
+// faster per query than 8 (B=4, H=1, N=188,416, d=64: 48.3 -> 47.2 ms; H=2,
+// d=72: 29.4 -> 28.8 ms), but in coarser work items. All compute every dQ row
+// with the same operations in the same order, so the choice changes no bit.
 template <int D, int KS>
-static hipError_t dq_8_or_12(const BwdArgs& a, double rate12) {
-  const int s8 = dq_resident_workgroups<D, 8, KS>(), s12 = dq_resident_workgroups<D, 12, KS>();
-  if (s8 <= 0 || s12 <= 0) return dq_v<D, 8, KS>(a);
-  const long long t8 = (long long)a.BH * ((a.Nq + 255) / 256), t12 = (long long)a.BH * ((a.Nq + 383) / 384);
-  const double c8 = (double)((t8 + s8 - 1) / s8) * 8.0, c12 = (double)((t12 + s12 - 1) / s12) * 12.0 / rate12;
-  return c12 < c8 ? dq_v<D, 12, KS>(a) : dq_v<D, 8, KS>(a);
+static hipError_t dq_d(const BwdArgs& a) {
+  const double c8 = launch_cost(a.BH, a.Nq, 8, dq_resident<D, 8, KS>());
+  const double c4 = launch_cost(a.BH, a.Nq, 4, dq_resident<D, 4, KS>());
+  if constexpr (KS <= 5) {
+    const double c12 = launch_cost(a.BH, a.Nq, 12, dq_resident<D, 12, KS>()) / 1.02;
+    if (c12 < c8 && c12 < c4) return dq_v<D, 12, KS>(a);
+  }
+  return c4 < c8 ? dq_v<D, 4, KS>(a) : dq_v<D, 8, KS>(a);
 }
 
 hipError_t launch_bwd_dq(const BwdArgs& a) {
   if (a.ds != nullptr) return launch_bwd_dq_ds(a);
   switch (tile_width(a.d)) {
-    case 64: return dq_8_or_12<64, 4>(a, 1.06);
-    case 96: return a.d <= 80 ? dq_8_or_12<96, 5>(a, 1.045) : dq_v<96, 8>(a);  // d <= 80: five contraction steps
-    case 128: return dq_v<128, 8>(a);
-    default: return dq_v<160, 8>(a);
+    case 64: return dq_d<64, 4>(a);
+    case 96: return a.d <= 80 ? dq_d<96, 5>(a) : dq_d<96, 6>(a);  // d <= 80: five contraction steps
+    case 128: return dq_d<128, 8>(a);
+    default: return dq_d<160, 10>(a);
   }
 }
 
