@@ -71,12 +71,13 @@ constexpr int kDkvBQ = 64;              // queries per streamed tile
 constexpr int kDkvAhead = 2;            // LDS operand reads this many matrix-core ops ahead (3 measured no better)
 
 // Direct global -> LDS copy of a tile's row statistics: 64 floats of D and
-// 64 of LSE*log2(e) (one dword per lane; rows past the end read as zeros).
-// Every wave copies the same data, so that all waves issue the same number
-// of loads per tile and one vmcnt bound fits them all.
-__device__ __forceinline__ void stats_dma(rsrc_t rd, rsrc_t rl, int row0, float* lds_stats, int lane) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(rd, (lds_void_t*)(lds_stats), 4, (row0 + lane) * 4, 0, 0, 0);
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(rl, (lds_void_t*)(lds_stats + kDkvBQ), 4, (row0 + lane) * 4, 0, 0, 0);
+// 64 of LSE*log2(e) (one dword per lane; rows past the end read as zeros), by
+// one wave each (`wave` a scalar).
+__device__ __forceinline__ void stats_dma(rsrc_t rd, rsrc_t rl, int row0, float* lds_stats, int lane, int wave) {
+  if (wave == 0)
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rd, (lds_void_t*)(lds_stats), 4, (row0 + lane) * 4, 0, 0, 0);
+  if (wave == 1)
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rl, (lds_void_t*)(lds_stats + kDkvBQ), 4, (row0 + lane) * 4, 0, 0, 0);
 }
 
 // One workgroup = 2*KBW waves = 32*KBW*KPW keys of one (b, h): KBW pairs of
@@ -239,7 +240,10 @@ __global__ __launch_bounds__(128 * KBW, KBW / 2) __attribute__((amdgpu_waves_per
   rf.init(lane);
   TrFrag<D> tf;
   tf.init(lane);
-  constexpr int DMA_PER_TILE = 2 * decltype(dma)::PER_WAVE + 2;  // loads per wave per tile
+  // A tile's requests: Q, dO, then the statistics (by waves 0 and 1, which fetch in both modes)
+  constexpr int PW = decltype(dma)::PER_WAVE;
+  constexpr int NREQ = 2 * PW + 1;
+  const int wave_s = __builtin_amdgcn_readfirstlane(wave);
 
   f32x16 acc[KPW][NCB];  // dV^T (role P) or dK^T (role dS) per key block
 #pragma unroll
@@ -299,18 +303,26 @@ __global__ __launch_bounds__(128 * KBW, KBW / 2) __attribute__((amdgpu_waves_per
     }
   };
 
-  auto issue_tile = [&](auto slot_tag, int t) {
+  auto issue_request = [&](auto slot_tag, int t, int r) __attribute__((always_inline)) {
     constexpr int SL = decltype(slot_tag)::value;
     const int row0 = (t0 + t) * kDkvBQ;
-    dma.issue(rq, row0, ldq, qbuf[SL]);
-    dmg.issue(rg, row0, ldg, gbuf[SL]);
-    stats_dma(rd, rl, row0, sbuf[SL], lane);
+    if (r < PW)
+      dma.issue_one(rq, row0, ldq, qbuf[SL], r);
+    else if (r < 2 * PW)
+      dmg.issue_one(rg, row0, ldg, gbuf[SL], r - PW);
+    else
+      stats_dma(rd, rl, row0, sbuf[SL], lane, wave_s);
+  };
+  auto issue_tile = [&](auto slot_tag, int t) __attribute__((always_inline)) {
+#pragma unroll
+    for (int r = 0; r < NREQ; ++r) issue_request(slot_tag, t, r);
   };
 
   // One tile of one role, in ring slot SL. Role P: S/P/dV; role dS: dP/dS/dK.
-  // The row statistics (and role dS's P) of both query blocks are read
-  // before `prefetch` requests the next tile, so that none of these LDS
-  // reads has to wait for that DMA. The widest tile, and waves with more than
+  // `prefetch(r)` makes request r of the next tile. The requests ride on the
+  // first odd ops: each holds a wave up for ~50 cycles, and all of them at the
+  // start of the tile, right behind the barrier, left the matrix cores to
+  // wait for every wave's burst at once. The widest tile, and waves with more than
   // one key block, have no registers to spare for both blocks: there block
   // 1's are read into block 0's registers once block 0's vector work is done
   // (end of phase 2). Role dS starts each dP accumulator at the block's -D
@@ -407,8 +419,6 @@ __global__ __launch_bounds__(128 * KBW, KBW / 2) __attribute__((amdgpu_waves_per
 #pragma unroll
     for (int a = 0; a < AH; ++a) aq[a] = read_a(a);
     sched_fence();
-    prefetch();
-    sched_fence();
     // every op index a compile-time constant (the widest tile's stream is too
     // long for the unroller's size limit, and register arrays indexed at run
     // time would live in scratch memory)
@@ -439,6 +449,7 @@ __global__ __launch_bounds__(128 * KBW, KBW / 2) __attribute__((amdgpu_waves_per
         acc[kp][j % NCB] = mfma32(aq[a % (AH + 1)], ob[kp][qb][j / NCB], acc[kp][j % NCB]);
         if constexpr (ph == 2) valu(kp, 1, j, P2);
       }
+      if constexpr (i % 2 == 1 && i / 2 < NREQ) prefetch(i / 2);
       sched_fence();
     });
     __builtin_amdgcn_s_setprio(0);
@@ -478,15 +489,14 @@ __global__ __launch_bounds__(128 * KBW, KBW / 2) __attribute__((amdgpu_waves_per
                        __attribute__((always_inline)) {
     constexpr bool RP = decltype(role_tag)::value;
     // tile t+1 past the end: zero rows, never read
-    auto prefetch = [&]() {
-      if constexpr (!STORE_DS || RP) issue_tile(slot_next, t + 1);
+    auto prefetch = [&](int r) __attribute__((always_inline)) {
+      if constexpr (!STORE_DS || RP) issue_request(slot_next, t + 1, r);
     };
     if constexpr (RP) {
-      if (run) run_tile(RoleP{}, slot_p, t, prefetch);
-      else prefetch();
+      run_tile(RoleP{}, slot_p, t, prefetch);
     } else {
       if (run) run_tile(RoleDs{}, slot_ds, t - 1, prefetch);
-      else prefetch();
+      else if constexpr (!STORE_DS) issue_tile(slot_next, t + 1);
     }
     if constexpr (STORE_DS) {
       if constexpr (RP) wait_vmem();
@@ -506,7 +516,7 @@ __global__ __launch_bounds__(128 * KBW, KBW / 2) __attribute__((amdgpu_waves_per
     }
     // last: role dS on tile n_pad-1 (slot 0, since n_pad = 1 mod 3)
     if constexpr (!RP) {
-      run_tile(RoleDs{}, S0{}, n_pad - 1, [] {});
+      run_tile(RoleDs{}, S0{}, n_pad - 1, [](int) {});
       flush_ds();
     }
   };
@@ -514,11 +524,12 @@ __global__ __launch_bounds__(128 * KBW, KBW / 2) __attribute__((amdgpu_waves_per
   // allocation; the role is a run-time branch inside each iteration)
   auto both = [&](auto slot_p, auto slot_next, auto slot_ds, int t, bool do_p, bool do_ds)
                   __attribute__((always_inline)) {
+    auto prefetch = [&](int r) __attribute__((always_inline)) { issue_request(slot_next, t + 1, r); };
     if (role_p) {
-      if (do_p) run_tile(RoleP{}, slot_p, t, [&]() { issue_tile(slot_next, t + 1); });
+      if (do_p) run_tile(RoleP{}, slot_p, t, prefetch);
       else issue_tile(slot_next, t + 1);
     } else {
-      if (do_ds) run_tile(RoleDs{}, slot_ds, t - 1, [&]() { issue_tile(slot_next, t + 1); });
+      if (do_ds) run_tile(RoleDs{}, slot_ds, t - 1, prefetch);
       else issue_tile(slot_next, t + 1);
     }
     wait_vmem();
@@ -573,11 +584,10 @@ __global__ __launch_bounds__(128 * KBW, KBW / 2) __attribute__((amdgpu_waves_per
         both(S2{}, S0{}, S1{}, t + 1, true, true);
         both(S0{}, S1{}, S2{}, t + 2, true, true);
       }
-      if (!role_p) run_tile(RoleDs{}, S0{}, n_pad - 1, [] {});
+      if (!role_p) run_tile(RoleDs{}, S0{}, n_pad - 1, [](int) {});
       if (pass + 1 < n_pass) next_pass();
     }
   }
-  (void)DMA_PER_TILE;
 
   if (two_part) wait_vmem();  // the first partial's stores have completed
 #pragma unroll
