@@ -50,17 +50,17 @@
  *    results do not depend on the call it is part of: one call over H heads
  *    gives the bits of H single-head calls, whatever the grid or the CU
  *    count. The only atomics are in the dK/dV stage: when its last round of
- *    key-block workgroups would be at most half full, those key blocks are
- *    split over two workgroups (one per half of the query tiles) that add
- *    into dK and dV rows zeroed first by the same call; two fp32 adds onto
- *    zero give the same bits in either order. Every key block, split or
- *    not, sums its query tiles as the same two rounded partial sums (split
- *    at the middle query tile) and adds them, so splitting changes no bit.
- *    Which blocks split depends on the number of key-block workgroups
- *    (B*H*ceil(N/K), K = 128 keys, or in the default mode 256 at head dims up
- *    to 64 and 192 at 65-80) and the device's CU count, looked up once per
- *    device at the first backward call (no stream work, so a graph capture
- *    may hold it).
+ *    key-block workgroups would be at most half full, and there are 256 query
+ *    tiles of 64 or more, those key blocks are split over two workgroups (one
+ *    per half of the query tiles) that add into dK and dV rows zeroed first by
+ *    the same call; two fp32 adds onto zero give the same bits in either
+ *    order. With that many query tiles every key block, split or not, sums
+ *    them as the same two rounded partial sums (split near the middle query
+ *    tile) and adds them, and with fewer as one sum, so splitting changes no
+ *    bit. Which blocks split, and how many queries or keys a workgroup takes,
+ *    depends on the sizes and the device's CU count, looked up once per
+ *    device at the first call (no stream work, so a graph capture may hold
+ *    it).
  *  - Calls are thread-safe; concurrent calls on different streams are fine.
  */
 #ifndef VITATTN_H

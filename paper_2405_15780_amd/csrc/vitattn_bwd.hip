@@ -4,7 +4,8 @@
 //
 //   1. preprocess:  D_i = sum_c dO_ic O_ic    (HBM-bound; stored as -D_i)
 //   2. dK/dV kernel: one workgroup per 128 keys (in the recompute mode 256
-//      at head dims up to 64, 192 at head dims 65-80; 32 or 64 per wave, K
+//      at head dims up to 64, 192 at head dims 65-80, down to 64 on small
+//      grids; 32 or 64 per wave, K
 //      and V held in registers); streams Q, dO, LSE and D in tiles of 64
 //      queries:
 //        S = Q K^T, P = exp2(S*scale*log2e - LSE*log2e)
@@ -68,6 +69,18 @@ __global__ __launch_bounds__(256) void attn_bwd_rowdot_kernel(const uint16_t* __
 // ------------------------------------------------------------------ dK / dV
 
 constexpr int kDkvBQ = 64;              // queries per streamed tile
+// Query tile at which a key block's two partial sums part, for n tiles; 0: one
+// sum, and the block is never split over two workgroups. The middle, less what
+// makes the first pass a whole number of the kernel's three-tile trips after
+// its first tile. Two sums only serve the split, whose halves add with
+// scattered atomics (~180 us for 128 blocks of 128 keys x 128 columns) to save
+// half a workgroup's time in the last round, 0.9 us per tile: it pays from
+// about 200 tiles on. Below that the second pass, which drains and refills the
+// pipeline, was pure cost (H=256, N=1,024, d=64: 217 -> 153 us with one sum),
+// and where the split was used it was most of the time (H=32, N=1,024, d=64:
+// 223 -> 33 us without it; H=4, N=4,096, d=128: 261 us).
+constexpr int kDkvSplitTiles = 256;
+__host__ __device__ constexpr int dkdv_mid(int n) { return n < kDkvSplitTiles ? 0 : n / 2 - (n / 2 + 2) % 3; }
 constexpr int kDkvAhead = 2;            // LDS operand reads this many matrix-core ops ahead (3 measured no better)
 
 // Direct global -> LDS copy of a tile's row statistics: 64 floats of D and
@@ -83,7 +96,8 @@ __device__ __forceinline__ void stats_dma(rsrc_t rd, rsrc_t rl, int row0, float*
 // One workgroup = 2*KBW waves = 32*KBW*KPW keys of one (b, h): KBW pairs of
 // waves, each pair owning KPW blocks of 32 keys (KBW = 4, KPW = 1: 8 waves,
 // 128 keys; KBW = 4, KPW = 2 at the narrowest tile: 8 waves, 256 keys;
-// KBW = 6, KPW = 1 in the 96-wide tile at d <= 80: 12 waves, 192 keys). The
+// KBW = 6, KPW = 1 in the 96-wide tile at d <= 80: 12 waves, 192 keys; KBW =
+// 2, KPW = 1 on small grids: 4 waves, 64 keys). The
 // two waves of a pair split the roles (waves share the SIMDs round robin, so
 // the vector and matrix phases of the roles interleave):
 //   role P  (waves 0 .. KBW-1): holds K, accumulates dV^T.
@@ -149,6 +163,7 @@ __global__ __launch_bounds__(128 * KBW, KBW / 2) __attribute__((amdgpu_waves_per
   constexpr int RING = 3;
   constexpr int NWAVES = 2 * KBW;
   constexpr int BK = 32 * KBW * KPW;  // keys per workgroup
+  static_assert(KBW % 2 == 0, "two waves per SIMD, or one");
   static_assert(KPW == 1 || !STORE_DS, "stored dS blocks are laid out per wave of one key block");
   static_assert(KPW == 1 || D != 160, "the widest tile has no registers for a second key block");
   // One variable per ring slot: the compiler then knows that reading one
@@ -184,17 +199,17 @@ __global__ __launch_bounds__(128 * KBW, KBW / 2) __attribute__((amdgpu_waves_per
   } else {
     const int part = blockIdx.x - n_whole;
     work = n_whole + (part >> 1);
-    if (part & 1) t0 = n_qt_real >> 1;
-    else t1 = n_qt_real >> 1;
+    if (part & 1) t0 = dkdv_mid(n_qt_real);
+    else t1 = dkdv_mid(n_qt_real);
   }
   // Every key block sums its query tiles as two partial sums split at tile
-  // mid, each scaled and rounded on its own, then added: a split half adds
+  // mid (one sum where mid = 0, see dkdv_mid), each scaled and rounded on its own, then added: a split half adds
   // its partial onto the zeroed row; a whole block runs the tile loop twice,
   // over [0, mid) and [mid, n), storing the first partial in between and
   // adding the second to it at the end. The two fp32 adds onto zero commute,
   // so dK and dV have the same bits whether or not the grid splits the block
   // (and so for any grid shape or CU count).
-  const int mid = n_qt_real >> 1;
+  const int mid = dkdv_mid(n_qt_real);
   const bool two_part = !split && mid > 0;
   if (two_part) t1 = mid;
   const int bh = work / n_ktiles;
@@ -243,6 +258,7 @@ __global__ __launch_bounds__(128 * KBW, KBW / 2) __attribute__((amdgpu_waves_per
   // A tile's requests: Q, dO, then the statistics (by waves 0 and 1, which fetch in both modes)
   constexpr int PW = decltype(dma)::PER_WAVE;
   constexpr int NREQ = 2 * PW + 1;
+  static_assert(2 * NREQ <= NA * KPW, "a tile's requests fit its op stream");
   const int wave_s = __builtin_amdgcn_readfirstlane(wave);
 
   f32x16 acc[KPW][NCB];  // dV^T (role P) or dK^T (role dS) per key block
@@ -1093,11 +1109,11 @@ static hipError_t dkdv_s(const BwdArgs& a) {
   const int n_kt = (a.Nk + BK - 1) / BK;
   const int total = a.BH * n_kt;
   // A last round at most half full is split in two halves of the query range
-  // (when there are two query tiles to split), so that it takes half as long.
+  // (when the key blocks take two sums), so that it takes half as long.
   const int slots = dkdv_resident<D, STORE_DS, KBW, KPW, KS>().workgroups;
   const int tail = slots > 0 ? total % slots : 0;
   int n_whole = total;
-  if (tail > 0 && 2 * tail <= slots && (a.Nq + kDkvBQ - 1) / kDkvBQ >= 2) {
+  if (tail > 0 && 2 * tail <= slots && dkdv_mid((a.Nq + kDkvBQ - 1) / kDkvBQ) > 0) {
     n_whole = total - tail;
     hipLaunchKernelGGL(zero_key_blocks_kernel, dim3(2 * tail), dim3(256), 0, a.stream, a.dk, a.dv, a.mdk, a.mdv, a.H,
                        a.d, a.Nk, n_kt, n_whole, BK);
@@ -1108,26 +1124,60 @@ static hipError_t dkdv_s(const BwdArgs& a) {
                      a.d, a.Nq, a.Nk, n_kt, n_whole, a.scale * kLog2e, a.scale);
   return hipGetLastError();
 }
-// Four pairs of waves per workgroup, except where noted. At the narrowest
-// tile in the recompute mode each wave holds two 32-key blocks (222 VGPRs,
-// two waves per SIMD, 256 keys per workgroup), so every operand it reads
-// from LDS feeds two matrix-core ops and every Q / dO tile it streams serves
-// twice the keys: 8 % faster than six one-block pairs at three waves per
-// SIMD (B=4, H=1, N=188,416, d=64), with the same bits. At the wider tiles
-// two blocks per wave leave room for one wave per SIMD only, which measured
-// 5 % slower at d=128 and no faster at d=96. In the 96-wide tile a head dim
-// up to 80 contracts S and dP over five 16-column steps instead of six, and
-// the recompute mode then fits three waves per SIMD (168 VGPRs, two values
-// spilled outside the tile loop): six pairs, 192 keys per workgroup, 4-5 %
-// faster at d=72 on large grids, with the same bits. The dS mode keeps four
-// pairs of one-block waves (its stored dS blocks are laid out per 128 keys).
-template <int D>
+
+// Estimated time of a dK/dV launch: whole rounds of resident workgroups, then
+// the last one, alone on its CUs or two to a CU, or split. one, two: a round's
+// time with one and with two workgroups per CU, against one of the widest form.
+static double dkdv_cost(const BwdArgs& a, int keys, const Resident& r, double one, double two) {
+  if (r.workgroups <= 0) return one;
+  const long long n = (long long)a.BH * ((a.Nk + keys - 1) / keys);
+  const long long rounds = n / r.workgroups, left = n - rounds * r.workgroups;
+  const int n_qt = (a.Nq + kDkvBQ - 1) / kDkvBQ;
+  const double full = r.workgroups > r.cus ? two : one;
+  double last = left == 0 ? 0. : left <= r.cus ? one : full;
+  if (left > 0 && 2 * left <= r.workgroups && dkdv_mid(n_qt) > 0)
+    last = 0.5 * last + 0.8 * left / n_qt * keys * tile_width(a.d) / (128. * 128.);  // the halves' atomics
+  return rounds * full + last;
+}
+
+// The widest form at the narrowest tile in the recompute mode: each wave holds
+// two 32-key blocks (220 VGPRs, two waves per SIMD, 256 keys per workgroup),
+// so every operand it reads from LDS feeds two matrix-core ops and every Q /
+// dO tile it streams serves twice the keys: 8 % faster than six one-block
+// pairs at three waves per SIMD (B=4, H=1, N=188,416, d=64), with the same
+// bits. At the wider tiles two blocks per wave leave room for one wave per
+// SIMD only, which measured 5 % slower at d=128 and no faster at d=96. In the
+// 96-wide tile a head dim up to 80 contracts S and dP over five 16-column
+// steps instead of six, and the recompute mode then fits three waves per SIMD
+// (166 VGPRs): six pairs, 192 keys per workgroup, 4-5 % faster at d=72 on large grids, with
+// the same bits. The dS mode keeps four pairs of one-block waves (its stored
+// dS blocks are laid out per 128 keys).
+// Narrower forms (fewer keys per workgroup, the same ops per key block) run
+// where the widest leaves CUs idle, by the shorter estimated time. A round of
+// them against one of the widest, measured at N = 4,096 .. 16,384: d <= 64
+// four one-block pairs 0.59, two pairs 0.40 alone on a CU and 0.61 two to a
+// CU; d <= 80 four pairs 0.79, two pairs 0.52; else two pairs 0.62-0.67.
+// H=2, N=8,191, d=128: 310 -> 157 us; H=1, N=4,096, d=64: 99 -> 51 us.
+template <int D, int KS>
 static hipError_t dkdv_d(const BwdArgs& a) {
-  if constexpr (D == 96) {
-    if (a.d <= 80) return a.ds != nullptr ? dkdv_s<96, true, 4, 1, 5>(a) : dkdv_s<96, false, 6, 1, 5>(a);
+  if (a.ds != nullptr) return dkdv_s<D, true, 4, 1, KS>(a);
+  if constexpr (D == 64) {
+    const double wide = dkdv_cost(a, 256, dkdv_resident<D, false, 4, 2, KS>(), 1., 1.);
+    const double four = dkdv_cost(a, 128, dkdv_resident<D, false, 4, 1, KS>(), 0.59, 0.59);
+    const double two = dkdv_cost(a, 64, dkdv_resident<D, false, 2, 1, KS>(), 0.4, 0.61);
+    if (two < four && two < wide) return dkdv_s<D, false, 2, 1, KS>(a);
+    return four < wide ? dkdv_s<D, false, 4, 1, KS>(a) : dkdv_s<D, false, 4, 2, KS>(a);
+  } else if constexpr (KS == 5) {
+    const double wide = dkdv_cost(a, 192, dkdv_resident<D, false, 6, 1, KS>(), 1., 1.);
+    const double four = dkdv_cost(a, 128, dkdv_resident<D, false, 4, 1, KS>(), 0.79, 0.79);
+    const double two = dkdv_cost(a, 64, dkdv_resident<D, false, 2, 1, KS>(), 0.52, 0.79);
+    if (two < four && two < wide) return dkdv_s<D, false, 2, 1, KS>(a);
+    return four < wide ? dkdv_s<D, false, 4, 1, KS>(a) : dkdv_s<D, false, 6, 1, KS>(a);
+  } else {
+    const double wide = dkdv_cost(a, 128, dkdv_resident<D, false, 4, 1, KS>(), 1., 1.);
+    const double two = dkdv_cost(a, 64, dkdv_resident<D, false, 2, 1, KS>(), 0.65, 1.);
+    return two < wide ? dkdv_s<D, false, 2, 1, KS>(a) : dkdv_s<D, false, 4, 1, KS>(a);
   }
-  if (a.ds != nullptr) return dkdv_s<D, true, 4, 1>(a);
-  return dkdv_s<D, false, 4, D == 64 ? 2 : 1>(a);
 }
 
 #define VITATTN_DKDV_INSTANTIATE(D, S, KBW, KPW, KS)                                                           \
@@ -1138,6 +1188,13 @@ static hipError_t dkdv_d(const BwdArgs& a) {
       const Map, int, int, int, int, int, int, float, float);
 VITATTN_DKDV_INSTANTIATE(128, false, 4, 1, 8)
 VITATTN_DKDV_INSTANTIATE(64, false, 4, 2, 4)
+VITATTN_DKDV_INSTANTIATE(64, false, 4, 1, 4)
+VITATTN_DKDV_INSTANTIATE(64, false, 2, 1, 4)
+VITATTN_DKDV_INSTANTIATE(96, false, 4, 1, 5)
+VITATTN_DKDV_INSTANTIATE(96, false, 2, 1, 5)
+VITATTN_DKDV_INSTANTIATE(96, false, 2, 1, 6)
+VITATTN_DKDV_INSTANTIATE(128, false, 2, 1, 8)
+VITATTN_DKDV_INSTANTIATE(160, false, 2, 1, 10)
 VITATTN_DKDV_INSTANTIATE(96, false, 4, 1, 6)
 VITATTN_DKDV_INSTANTIATE(96, false, 6, 1, 5)
 VITATTN_DKDV_INSTANTIATE(160, false, 4, 1, 10)
@@ -1209,10 +1266,10 @@ hipError_t launch_bwd_rowdot(const BwdArgs& a) {
 }
 hipError_t launch_bwd_dkdv(const BwdArgs& a) {
   switch (tile_width(a.d)) {
-    case 64: return dkdv_d<64>(a);
-    case 96: return dkdv_d<96>(a);
-    case 128: return dkdv_d<128>(a);
-    default: return dkdv_d<160>(a);
+    case 64: return dkdv_d<64, 4>(a);
+    case 96: return a.d <= 80 ? dkdv_d<96, 5>(a) : dkdv_d<96, 6>(a);
+    case 128: return dkdv_d<128, 8>(a);
+    default: return dkdv_d<160, 10>(a);
   }
 }
 hipError_t launch_bwd_dq_ds(const BwdArgs& a) {

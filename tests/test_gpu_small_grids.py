@@ -41,3 +41,28 @@ def test_tile_edges_against_the_oracle(d, N):
     got = {n: np64(a) for n, a in run_hip(x, scale).items()}
     ref = oracle.forward_backward(x["q"], x["k"], x["v"], x["dout"], scale)
     assert_close(got, ref, label=f"small grids N={N} d={d}")
+
+
+# From 256 query tiles on, key blocks of a last round that is at most half full
+# are split over two workgroups. On 256 CUs these grids split 128 of 640 blocks
+# (d = 64, 128, 160) and 90 of 602 (d = 72); a single head splits none.
+@pytest.mark.parametrize("d,H,store_ds", [(64, 10, False), (72, 7, False), (128, 5, False), (128, 5, True), (160, 5, False)])
+def test_split_key_blocks_equal_whole_ones(d, H, store_ds):
+    t = torch()
+    B, N = 1, 16384 - 17
+    print(f"case split key blocks H={H} N={N} d={d} store_ds={store_ds}", flush=True)
+    x = workloads.make_small_inputs(B, H, N, d, seed=6300 + d)
+    scale = 1.0 / np.sqrt(d)
+    full = run_hip(x, scale, store_ds=store_ds)
+    for h in (0, H - 1):
+        one = run_hip({n: np.ascontiguousarray(a[:, h:h + 1]) for n, a in x.items()}, scale, store_ds=store_ds)
+        for name in ("o", "lse", "dq", "dk", "dv"):
+            assert t.equal(full[name][:, h:h + 1], one[name]), (name, h)
+    if d == 128 and not store_ds:
+        h = H - 1
+        lse, D = oracle.row_statistics(x["q"], x["k"], x["v"], x["dout"], scale, 0, h)
+        keys = np.sort(np.random.default_rng(d).choice(N, 32, replace=False))
+        dk, dv = oracle.key_rows(x["q"], x["k"], x["v"], x["dout"], scale, 0, h, keys, lse, D)
+        kk = t.from_numpy(keys).cuda()
+        assert_close({"dk": np64(full["dk"][0, h][kk]), "dv": np64(full["dv"][0, h][kk])}, {"dk": dk, "dv": dv},
+                     names=("dk", "dv"), label="split key blocks, sampled key rows")
