@@ -1290,7 +1290,9 @@ static Resident dq_resident() {
 // Waves per workgroup, by the shorter estimated time (launch_cost). Four
 // waves, one per SIMD, take 0.66-0.86 of the time of eight on a CU, so grids
 // that leave CUs idle with 256 queries per workgroup take them (B=1, H=2,
-// N=16,384, d=128: 400 -> 345 us; N=4,096: 119 -> 75 us). At d <= 80 the kernel fits
+// N=16,384, d=128: 400 -> 345 us; N=4,096: 119 -> 75 us). Where several share a CU (d <= 96) short
+// sequences take them on full grids too: one's start and end overlap another's
+// tiles (H=256, N=1,024, d=64: 130 -> 112 us). At d <= 80 the kernel fits
 // three waves per SIMD (three to five values spilled, outside the loop but for
 // one operand at D = 96): 12 waves (384 queries) share each K / V tile, 2 %
 // faster per query than 8 (B=4, H=1, N=188,416, d=64: 48.3 -> 47.2 ms; H=2,
@@ -1298,10 +1300,10 @@ static Resident dq_resident() {
 // with the same operations in the same order, so the choice changes no bit.
 template <int D, int KS>
 static hipError_t dq_d(const BwdArgs& a) {
-  const double c8 = launch_cost(a.BH, a.Nq, 8, dq_resident<D, 8, KS>());
-  const double c4 = launch_cost(a.BH, a.Nq, 4, dq_resident<D, 4, KS>());
+  const double c8 = launch_cost(a.BH, a.Nq, a.Nk, 8, dq_resident<D, 8, KS>());
+  const double c4 = launch_cost(a.BH, a.Nq, a.Nk, 4, dq_resident<D, 4, KS>());
   if constexpr (KS <= 5) {
-    const double c12 = launch_cost(a.BH, a.Nq, 12, dq_resident<D, 12, KS>()) / 1.02;
+    const double c12 = launch_cost(a.BH, a.Nq, a.Nk, 12, dq_resident<D, 12, KS>()) / 1.02;
     if (c12 < c8 && c12 < c4) return dq_v<D, 12, KS>(a);
   }
   return c4 < c8 ? dq_v<D, 4, KS>(a) : dq_v<D, 8, KS>(a);

@@ -364,7 +364,10 @@ static Resident fwd_resident() {
 // 8 waves on it, two 1.02-1.05, three (d <= 64) 1.48 (measured at N = 16,384,
 // H = 1 .. 16, every width), so grids up to one per CU and those with a
 // nearly empty last round take it: B=1, H=1, N=1,024, d=64 20.3 -> 15.1 us,
-// B=1, H=2, N=16,384, d=128 334 -> 277 us. At the narrowest tile the kernel's
+// B=1, H=2, N=16,384, d=128 334 -> 277 us. Short sequences take it on
+// full grids too, as one workgroup's start and end overlap another's tiles
+// (H=256, N=1,024: d=64 101 -> 91 us, d=160 216 -> 204; N=512, d=64 32.5 ->
+// 29.1). At the narrowest tile the kernel's
 // ~160 VGPRs fit three waves per SIMD: 12 waves (384 queries) share each K /
 // V tile, ~5 % faster per query than 8 (N = 188,416 and 1,048,576), but in
 // coarser work items. Each query row is computed by the same operations in
@@ -373,9 +376,9 @@ template <int D, int KB, int KS>
 static hipError_t launch_fwd_d(const FwdArgs& a) {
   constexpr int MINW4 = D == 64 ? 3 : 2;
   const Resident r8 = fwd_resident<D, KB, 8, 2, KS>(), r4 = fwd_resident<D, KB, 4, MINW4, KS>();
-  const double c8 = launch_cost(a.BH, a.Nq, 8, r8), c4 = launch_cost(a.BH, a.Nq, 4, r4);
+  const double c8 = launch_cost(a.BH, a.Nq, a.Nk, 8, r8), c4 = launch_cost(a.BH, a.Nq, a.Nk, 4, r4);
   if constexpr (D == 64) {
-    const double c12 = launch_cost(a.BH, a.Nq, 12, fwd_resident<D, KB, 12, 3, KS>()) / 1.05;
+    const double c12 = launch_cost(a.BH, a.Nq, a.Nk, 12, fwd_resident<D, KB, 12, 3, KS>()) / 1.05;
     if (c12 < c8 && c12 < c4) return launch_fwd_v<D, KB, 12, 3, KS>(a);
   }
   return c4 < c8 ? launch_fwd_v<D, KB, 4, MINW4, KS>(a) : launch_fwd_v<D, KB, 8, 2, KS>(a);

@@ -38,18 +38,22 @@ class ResidentCache {
 
 // Estimated time of a forward or dQ launch of `nw` waves (32 nw query rows)
 // per workgroup, in units of one round of 8-wave workgroups, one per CU:
-// whole rounds, then the last one by how many workgroups a CU gets. Only
-// 4-wave workgroups are ever resident in numbers on a CU. Without the
-// device's figures 8 waves win.
-inline double launch_cost(int BH, int Nq, int nw, const Resident& r) {
+// whole rounds, then the last one by how many workgroups a CU gets, and the
+// start and end of each workgroup, worth so many 64-key tiles. Only 4-wave
+// workgroups share a CU, and then one's start and end overlap another's tiles.
+// Without the device's figures 8 waves win.
+inline double launch_cost(int BH, int Nq, int Nk, int nw, const Resident& r) {
   if (r.workgroups <= 0) return nw == 8 ? 0. : 1.;
   const long long n = (long long)BH * ((Nq + 32 * nw - 1) / (32 * nw));
   const long long rounds = n / r.workgroups, left = n - rounds * r.workgroups;
-  if (nw != 4) return (double)(rounds + (left > 0)) * (nw / 8.);
-  constexpr double of[4] = {0., 0.86, 1.04, 1.5};  // 1 .. 3 per CU: measured 0.66-0.86, 1.02-1.05, 1.48-1.52
+  const double tiles = (Nk + 63) / 64, alone = 1. + 6. / tiles;
+  if (nw != 4) return (double)(rounds + (left > 0)) * (nw / 8.) * alone;
+  // 1 .. 3 per CU: measured 0.66-0.86, 1.02-1.05, 1.48-1.52; the ends 3-4.6
+  // tiles' time with company, 6-7 alone (N = 512 .. 16,384, every width)
+  constexpr double of[4] = {0., 0.86, 1.04, 1.5};
   const int per_cu = r.workgroups / r.cus < 3 ? r.workgroups / r.cus : 3;
   const int last = (int)((left + r.cus - 1) / r.cus);
-  return rounds * of[per_cu] + of[last < per_cu ? last : per_cu];
+  return (rounds * of[per_cu] + of[last < per_cu ? last : per_cu]) * (per_cu > 1 ? 1. + 4.5 / tiles : alone);
 }
 
 // Where the rows of one [B][H][N][d] operand live: element strides of the
