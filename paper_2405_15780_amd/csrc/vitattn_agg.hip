@@ -18,7 +18,7 @@
 // summed over its d/8 lanes by an exchange butterfly (every lane of the row
 // ends with the same, bitwise equal value); weighted sums over rows stay
 // per lane and are summed across a chunk's rows once, at the end. A wave
-// issues the loads of several chunks before using any of them.
+// issues the loads of several chunks (agg_group) before using any of them.
 // dq is reduced without atomics: each block sums a fixed range of patches
 // into a partial in the workspace, then one pass adds the partials in a fixed
 // order, so results are bitwise reproducible.
@@ -87,6 +87,13 @@ __device__ __forceinline__ void chunk_rows_sum(float (&x)[8]) {
 
 __device__ __forceinline__ uint4 load16(const uint16_t* p) { return *reinterpret_cast<const uint4*>(p); }
 
+// G pieces of consecutive chunks (zeros where ok[u] is false)
+template <int G>
+__device__ __forceinline__ void load_chunks(const uint16_t* p, const bool (&ok)[G], uint4 (&x)[G]) {
+#pragma unroll
+  for (int u = 0; u < G; ++u) x[u] = ok[u] ? load16(p + (size_t)u * 512) : make_uint4(0u, 0u, 0u, 0u);
+}
+
 __device__ __forceinline__ void store8(float* p, const float (&x)[8]) {
   reinterpret_cast<float4*>(p)[0] = make_float4(x[0], x[1], x[2], x[3]);
   reinterpret_cast<float4*>(p)[1] = make_float4(x[4], x[5], x[6], x[7]);
@@ -94,12 +101,12 @@ __device__ __forceinline__ void store8(float* p, const float (&x)[8]) {
 
 }  // namespace
 
-template <int D>
+template <int D, int G>
 __global__ __launch_bounds__(256) void attn_agg_fwd_kernel(const uint16_t* __restrict__ q,
                                                            const uint16_t* __restrict__ k,
                                                            const uint16_t* __restrict__ v, float* __restrict__ o,
                                                            float* __restrict__ lse, int MH, int H, int C, float c2) {
-  constexpr int LPR = D / 8, RPC = 64 / LPR, G = kAggChunkGroup;
+  constexpr int LPR = D / 8, RPC = 64 / LPR;
   const int wave = threadIdx.x >> 6;
   const int inst = blockIdx.x * 4 + wave;
   if (inst >= MH) return;  // whole waves exit together; no block barrier follows
@@ -121,12 +128,9 @@ __global__ __launch_bounds__(256) void attn_agg_fwd_kernel(const uint16_t* __res
     uint4 kr[G], vr[G];
     bool ok[G];
 #pragma unroll
-    for (int u = 0; u < G; ++u) {
-      ok[u] = (t0 + u) * RPC + r < C;
-      kr[u] = ok[u] ? load16(kb + (size_t)(t0 + u) * 512) : make_uint4(0u, 0u, 0u, 0u);
-    }
-#pragma unroll
-    for (int u = 0; u < G; ++u) vr[u] = ok[u] ? load16(vb + (size_t)(t0 + u) * 512) : make_uint4(0u, 0u, 0u, 0u);
+    for (int u = 0; u < G; ++u) ok[u] = (t0 + u) * RPC + r < C;
+    load_chunks<G>(kb + (size_t)t0 * 512, ok, kr);
+    load_chunks<G>(vb + (size_t)t0 * 512, ok, vr);
     float s[G], mx = -INFINITY;
 #pragma unroll
     for (int u = 0; u < G; ++u) {
@@ -171,13 +175,13 @@ __global__ __launch_bounds__(256) void attn_agg_fwd_kernel(const uint16_t* __res
 // paper's C = 92 at d = 64) that is a single group of chunks. Each lane
 // accumulates ds_c k_c over the rows it holds, and the rows of a chunk are
 // summed once at the end.
-template <int D>
+template <int D, int G>
 __global__ __launch_bounds__(256) void attn_agg_bwd_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const float* __restrict__ o, const uint16_t* __restrict__ dout, const float* __restrict__ lse,
     float* __restrict__ dk, float* __restrict__ dv, float* __restrict__ partial, int M, int H, int C, float c2,
     float scale) {
-  constexpr int LPR = D / 8, RPC = 64 / LPR, G = kAggChunkGroup;
+  constexpr int LPR = D / 8, RPC = 64 / LPR;
   __shared__ __attribute__((aligned(16))) float red[4][D];
   debug_poison_lds(red);
   const int h = blockIdx.x % H, mb = blockIdx.x / H;
@@ -205,13 +209,9 @@ __global__ __launch_bounds__(256) void attn_agg_bwd_kernel(
       uint4 kr[G], vr[G];
       bool ok[G];
 #pragma unroll
-      for (int u = 0; u < G; ++u) {
-        ok[u] = (t0 + u) * RPC + r < C;
-        kr[u] = ok[u] ? load16(k + base + (size_t)(t0 + u) * 512) : make_uint4(0u, 0u, 0u, 0u);
-      }
-#pragma unroll
-      for (int u = 0; u < G; ++u)
-        vr[u] = ok[u] ? load16(v + base + (size_t)(t0 + u) * 512) : make_uint4(0u, 0u, 0u, 0u);
+      for (int u = 0; u < G; ++u) ok[u] = (t0 + u) * RPC + r < C;
+      load_chunks<G>(k + base + (size_t)t0 * 512, ok, kr);
+      load_chunks<G>(v + base + (size_t)t0 * 512, ok, vr);
 #pragma unroll
       for (int u = 0; u < G; ++u) {
         float kx[8], vx[8];
@@ -275,34 +275,56 @@ __global__ __launch_bounds__(1024) void attn_agg_dq_kernel(const float* __restri
   }
 }
 
-#define VITATTN_AGG_INSTANTIATE(D)                                                                             \
-  template __global__ void attn_agg_fwd_kernel<D>(const uint16_t* __restrict__, const uint16_t* __restrict__, \
-                                                  const uint16_t* __restrict__, float* __restrict__,          \
-                                                  float* __restrict__, int, int, int, float);                 \
-  template __global__ void attn_agg_bwd_kernel<D>(                                                             \
+#define VITATTN_AGG_FWD_INSTANTIATE(D, G)                                                                        \
+  template __global__ void attn_agg_fwd_kernel<D, G>(const uint16_t* __restrict__, const uint16_t* __restrict__, \
+                                                     const uint16_t* __restrict__, float* __restrict__,       \
+                                                     float* __restrict__, int, int, int, float);
+#define VITATTN_AGG_BWD_INSTANTIATE(D, G)                                                                      \
+  template __global__ void attn_agg_bwd_kernel<D, G>(                                                         \
       const uint16_t* __restrict__, const uint16_t* __restrict__, const uint16_t* __restrict__,               \
       const float* __restrict__, const uint16_t* __restrict__, const float* __restrict__, float* __restrict__, \
       float* __restrict__, float* __restrict__, int, int, int, float, float);
-VITATTN_AGG_INSTANTIATE(64)
-VITATTN_AGG_INSTANTIATE(128)
-#undef VITATTN_AGG_INSTANTIATE
+// group sizes of the two passes (see agg_group)
+#define VITATTN_AGG_FWD_GROUPS(X, D) X(D, 1) X(D, 2) X(D, 3) X(D, 4) X(D, 6) X(D, 8) X(D, 10) X(D, 12)
+#define VITATTN_AGG_BWD_GROUPS(X, D) X(D, 1) X(D, 2) X(D, 3) X(D, 4) X(D, 12)
+VITATTN_AGG_FWD_GROUPS(VITATTN_AGG_FWD_INSTANTIATE, 64)
+VITATTN_AGG_FWD_GROUPS(VITATTN_AGG_FWD_INSTANTIATE, 128)
+VITATTN_AGG_BWD_GROUPS(VITATTN_AGG_BWD_INSTANTIATE, 64)
+VITATTN_AGG_BWD_GROUPS(VITATTN_AGG_BWD_INSTANTIATE, 128)
+#undef VITATTN_AGG_FWD_INSTANTIATE
+#undef VITATTN_AGG_BWD_INSTANTIATE
 
 // dq partials of the backward pass: one per block of four patches
 int agg_partials(int M) { return (M + 3) / 4; }
 
-template <int D>
-static hipError_t agg_fwd_d(const AggArgs& a) {
+// Chunks whose loads a wave issues together: the patch's chunks in as few
+// groups of at most kAggChunkGroup as they fit, evenly, rounded up to a size
+// that is instantiated. A fixed group of 12 went through its arithmetic for
+// chunks a patch doesn't have and held their registers: M=2,000, H=16, d=64,
+// C=8 (one chunk) forward 37.1 -> 16.9 us, backward 87 -> 39 us; M=8,192, C=24
+// (three) 184 -> 132 us and 495 -> 477 us. The backward takes groups of 12
+// from five chunks on: with smaller ones more waves are in flight and their
+// stores come between other waves' loads (M=8,192, H=16, C=33: 605 us in groups
+// of 12, 651 in groups of 6).
+static int agg_group(int C, int d) {
+  const int chunks = (C + 512 / d - 1) / (512 / d);
+  const int groups = (chunks + kAggChunkGroup - 1) / kAggChunkGroup;
+  return (chunks + groups - 1) / groups;
+}
+
+template <int D, int G>
+static hipError_t agg_fwd_g(const AggArgs& a) {
   const int MH = a.M * a.H;
-  hipLaunchKernelGGL(attn_agg_fwd_kernel<D>, dim3((unsigned)((MH + 3) / 4)), dim3(256), 0, a.stream, a.q, a.k, a.v,
-                     a.o_out, a.lse_out, MH, a.H, a.C, a.scale * kLog2e);
+  hipLaunchKernelGGL((attn_agg_fwd_kernel<D, G>), dim3((unsigned)((MH + 3) / 4)), dim3(256), 0, a.stream, a.q, a.k,
+                     a.v, a.o_out, a.lse_out, MH, a.H, a.C, a.scale * kLog2e);
   return hipGetLastError();
 }
 
-template <int D>
-static hipError_t agg_bwd_d(const AggArgs& a) {
+template <int D, int G>
+static hipError_t agg_bwd_g(const AggArgs& a) {
   const int parts = agg_partials(a.M);
-  hipLaunchKernelGGL(attn_agg_bwd_kernel<D>, dim3((unsigned)(parts * a.H)), dim3(256), 0, a.stream, a.q, a.k, a.v,
-                     a.o, a.dout, a.lse, a.dk, a.dv, a.partial, a.M, a.H, a.C, a.scale * kLog2e, a.scale);
+  hipLaunchKernelGGL((attn_agg_bwd_kernel<D, G>), dim3((unsigned)(parts * a.H)), dim3(256), 0, a.stream, a.q, a.k,
+                     a.v, a.o, a.dout, a.lse, a.dk, a.dv, a.partial, a.M, a.H, a.C, a.scale * kLog2e, a.scale);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int HD = a.H * D;
@@ -310,6 +332,27 @@ static hipError_t agg_bwd_d(const AggArgs& a) {
                      parts, HD, a.scale);
   return hipGetLastError();
 }
+
+template <int D>
+static hipError_t agg_fwd_d(const AggArgs& a) {
+  const int g = agg_group(a.C, D);
+#define VITATTN_AGG_LAUNCH(D_, G) \
+  if (g <= G) return agg_fwd_g<D_, G>(a);
+  VITATTN_AGG_FWD_GROUPS(VITATTN_AGG_LAUNCH, D)
+#undef VITATTN_AGG_LAUNCH
+  return hipErrorInvalidValue;
+}
+template <int D>
+static hipError_t agg_bwd_d(const AggArgs& a) {
+  const int g = agg_group(a.C, D);
+#define VITATTN_AGG_LAUNCH(D_, G) \
+  if (g <= G) return agg_bwd_g<D_, G>(a);
+  VITATTN_AGG_BWD_GROUPS(VITATTN_AGG_LAUNCH, D)
+#undef VITATTN_AGG_LAUNCH
+  return hipErrorInvalidValue;
+}
+#undef VITATTN_AGG_FWD_GROUPS
+#undef VITATTN_AGG_BWD_GROUPS
 
 hipError_t launch_agg_fwd(const AggArgs& a) { return a.d == 128 ? agg_fwd_d<128>(a) : agg_fwd_d<64>(a); }
 hipError_t launch_agg_bwd(const AggArgs& a) { return a.d == 128 ? agg_bwd_d<128>(a) : agg_bwd_d<64>(a); }
