@@ -239,6 +239,23 @@ int vitattn_bwd_strided(const void* q, vitattn_strides sq, const void* k, vitatt
                         vitattn_strides sdk, float* dv, vitattn_strides sdv, int B, int H, int Nq, int Nk, int d,
                         float scale, int flags, void* workspace, size_t workspace_bytes, void* stream);
 
+/*
+ * The backward pass of a bf16 training step: vitattn_bwd_strided (flags = 0)
+ * with the conversions around it done by its kernels. grad is the fp32
+ * gradient with respect to o (layout sg, strides multiples of 4); it is
+ * rounded to bf16 into dout (bf16 [B][H][Nq][d], dense, written), which takes
+ * the place of vitattn_bwd's dout. dq is written as bf16 [B][H][Nq][d], dk and
+ * dv as bf16 [B][H][Nk][d] where vitattn_bwd_train_bf16_kv(Nq) is 1 and as
+ * fp32 otherwise, all dense. The values are those of the separate conversions
+ * (round to nearest even), bit for bit. dout must not alias grad. The other
+ * arguments, the validation and the status are vitattn_bwd_strided's.
+ */
+int vitattn_bwd_train_bf16_kv(int Nq);
+int vitattn_bwd_train(const void* q, vitattn_strides sq, const void* k, vitattn_strides sk, const void* v,
+                      vitattn_strides sv, const float* o, vitattn_strides so, const float* grad, vitattn_strides sg,
+                      const float* lse, void* dout, void* dq, void* dk, void* dv, int B, int H, int Nq, int Nk, int d,
+                      float scale, void* workspace, size_t workspace_bytes, void* stream);
+
 /* The two kernels of the dS mode as separate calls (dense operands, Nq = Nk =
  * N; the row-statistics stage vitattn_bwd_rowdot runs first), for timing each:
  * vitattn_bwd_dkdv_ds writes dK, dV and the dS blocks into the workspace,

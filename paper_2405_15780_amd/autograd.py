@@ -4,7 +4,9 @@ backward are the library's kernels (argument marshalling only).
 attention(q, k, v) takes bf16 [B, H, Nq, d] queries and [B, H, Nk, d] keys
 and values (any strides with d contiguous) and returns O in fp32. In the
 backward, the upstream gradient is rounded to bf16 (the kernels' dO operand)
-and dQ, dK, dV, computed in fp32, are returned in the inputs' dtype.
+and dQ, dK, dV, computed in fp32, are returned in the inputs' dtype. For an
+fp32 gradient with unit stride along d the kernels do both conversions
+(binding.bwd_train); others are converted around binding.bwd, to the same bits.
 """
 from __future__ import annotations
 
@@ -36,6 +38,10 @@ class _Attention:
                 @staticmethod
                 def backward(ctx, grad_o):
                     q, k, v, o, lse = ctx.saved_tensors
+                    if not ctx.store_ds:
+                        grads = _b.bwd_train(q, k, v, o, lse, grad_o, ctx.scale)
+                        if grads is not None:
+                            return *grads, None, None
                     dout = grad_o.to(torch.bfloat16)
                     if dout.stride(-1) != 1:
                         dout = dout.contiguous()

@@ -42,6 +42,9 @@ _SIGNATURES = {
     "vitattn_fwd_strided": (c_int, [c_void_p, _S] * 4 + [c_void_p] + [c_int] * 5 + [c_float, c_void_p]),
     "vitattn_bwd_strided": (c_int, [c_void_p, _S] * 5 + [c_void_p] + [c_void_p, _S] * 3 + [c_int] * 5
                             + [c_float, c_int, c_void_p, c_size_t, c_void_p]),
+    "vitattn_bwd_train_bf16_kv": (c_int, [c_int]),
+    "vitattn_bwd_train": (c_int, [c_void_p, _S] * 5 + [c_void_p] * 5 + [c_int] * 5
+                          + [c_float, c_void_p, c_size_t, c_void_p]),
     "vitattn_merge": (c_int, [c_void_p] * 2 + [c_int] + [c_void_p] * 2 + [c_int] * 4 + [c_void_p]),
     "vitattn_agg_fwd": (c_int, [c_void_p] * 5 + [c_int] * 4 + [c_float, c_void_p]),
     "vitattn_agg_bwd_workspace_bytes": (c_size_t, [c_int] * 4),
@@ -256,6 +259,34 @@ def bwd(q, k, v, o, lse, dout, scale=None, workspace=None, out=None, accumulate_
                                 _default_scale(d, scale), flags, ws.data_ptr(), ws_bytes, _stream_ptr(q))
     _check(st)
     return dq, dk, dv
+
+
+def bwd_train(q, k, v, o, lse, grad, scale=None):
+    """Gradients of q, k and v in bf16 for an fp32 upstream gradient: bwd() with
+    grad rounded to bf16 before and its outputs after, the conversions done in
+    its kernels where they can be. None if grad's layout needs the general path."""
+    torch = _torch()
+    _as_input(q, "q")
+    for t, n in ((k, "k"), (v, "v")):
+        _as_input(t, n, q.device)
+    B, H, Nq, Nk, d = _kv_shapes(q, k, v)
+    _expect(o, "o", torch.float32, (B, H, Nq, d), q.device)
+    _expect(lse, "lse", torch.float32, (B, H, Nq), q.device, dense=True)
+    s = grad.stride()
+    if not (grad.is_cuda and grad.device == q.device and grad.dtype == torch.float32 and grad.shape == q.shape
+            and s[3] == 1 and s[2] >= grad.shape[3] and all(x >= 0 and x % 4 == 0 for x in s[:3])
+            and grad.data_ptr() % 16 == 0):
+        return None
+    lib = library()
+    dout, dq = (torch.empty((B, H, Nq, d), dtype=torch.bfloat16, device=q.device) for _ in range(2))
+    kv_type = torch.bfloat16 if lib.vitattn_bwd_train_bf16_kv(Nq) else torch.float32
+    dk, dv = (torch.empty((B, H, Nk, d), dtype=kv_type, device=q.device) for _ in range(2))
+    ws, ws_bytes = _workspace(q, k, None)
+    _check(lib.vitattn_bwd_train(q.data_ptr(), strides_of(q), k.data_ptr(), strides_of(k), v.data_ptr(),
+                                 strides_of(v), o.data_ptr(), strides_of(o), grad.data_ptr(), strides_of(grad),
+                                 lse.data_ptr(), dout.data_ptr(), dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), B, H,
+                                 Nq, Nk, d, _default_scale(d, scale), ws.data_ptr(), ws_bytes, _stream_ptr(q)))
+    return dq, dk.to(torch.bfloat16), dv.to(torch.bfloat16)
 
 
 VITATTN_NOALLOC_MAX_ROWS = 4194304

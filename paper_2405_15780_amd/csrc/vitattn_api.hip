@@ -225,6 +225,10 @@ static vitattn::BwdArgs bwd_args(const void* q, const void* k, const void* v, co
   a.d = d;
   a.scale = scale;
   a.accumulate_dq = accumulate_dq;
+  a.grad = nullptr;
+  a.mgrad = a.mq;
+  a.dout_w = nullptr;
+  a.dq16 = a.kv16 = false;
   a.stream = static_cast<hipStream_t>(stream);
   return a;
 }
@@ -279,6 +283,43 @@ int vitattn_bwd_strided(const void* q, vitattn_strides sq, const void* k, vitatt
     a.mdq = to_map(sdq);
     a.mdk = to_map(sdk);
     a.mdv = to_map(sdv);
+    return vitattn::launch_bwd(a) == hipSuccess ? VITATTN_OK : VITATTN_E_HIP;
+  } catch (...) {
+    return VITATTN_E_INTERNAL;
+  }
+}
+
+int vitattn_bwd_train_bf16_kv(int Nq) { return Nq >= 1 && vitattn::dkdv_one_sum(Nq) ? 1 : 0; }
+
+int vitattn_bwd_train(const void* q, vitattn_strides sq, const void* k, vitattn_strides sk, const void* v,
+                      vitattn_strides sv, const float* o, vitattn_strides so, const float* grad, vitattn_strides sg,
+                      const float* lse, void* dout, void* dq, void* dk, void* dv, int B, int H, int Nq, int Nk, int d,
+                      float scale, void* workspace, size_t workspace_bytes, void* stream) {
+  try {
+    int st = check_sizes_kv(B, H, Nq, Nk, d);
+    if (st != VITATTN_OK) return st;
+    if (!bwd_items_ok(B, H, Nq, Nk, d)) return VITATTN_E_INVAL;
+    if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(o) || !aligned16(grad) || !aligned16(lse) ||
+        !aligned16(dout) || !aligned16(dq) || !aligned16(dk) || !aligned16(dv))
+      return VITATTN_E_INVAL;
+    if (!scale_ok(scale)) return VITATTN_E_INVAL;
+    if (check_map(sq, B, H, Nq, d, 2, false) || check_map(sk, B, H, Nk, d, 2, false) ||
+        check_map(sv, B, H, Nk, d, 2, false) || check_map(so, B, H, Nq, d, 4, false) ||
+        check_map(sg, B, H, Nq, d, 4, false))
+      return VITATTN_E_INVAL;
+    st = check_workspace(workspace, workspace_bytes, B, H, Nq, d);
+    if (st != VITATTN_OK) return st;
+    vitattn::BwdArgs a = bwd_args(q, k, v, o, dout, lse, static_cast<float*>(dq), static_cast<float*>(dk),
+                                  static_cast<float*>(dv), B, H, Nq, Nk, d, scale, false, workspace, stream);
+    a.mq = to_map(sq);
+    a.mk = to_map(sk);
+    a.mv = to_map(sv);
+    a.mo = to_map(so);
+    a.grad = grad;
+    a.mgrad = to_map(sg);
+    a.dout_w = static_cast<uint16_t*>(dout);
+    a.dq16 = true;
+    a.kv16 = vitattn::dkdv_one_sum(Nq);
     return vitattn::launch_bwd(a) == hipSuccess ? VITATTN_OK : VITATTN_E_HIP;
   } catch (...) {
     return VITATTN_E_INTERNAL;

@@ -38,8 +38,12 @@ namespace vitattn {
 // accumulator at it) and LSE_i * log2(e) (the logsumexp in the base-2 units
 // of the kernels' exp2). Each lives in its own region of the workspace. LPR
 // lanes per row take 8 columns each (lanes past the head dim add nothing).
-template <int LPR>
+// From an fp32 upstream gradient (grad) it also writes dout, dense: the
+// gradient rounded to bf16, which the statistics and the other kernels use.
+template <int LPR, bool GRAD32>
 __global__ __launch_bounds__(256) void attn_bwd_rowdot_kernel(const uint16_t* __restrict__ dout,
+                                                              const float* __restrict__ grad,
+                                                              uint16_t* __restrict__ dout_w,
                                                               const float* __restrict__ o,
                                                               const float* __restrict__ lse, float* __restrict__ drow,
                                                               float* __restrict__ lse2, const Map mg, const Map mo,
@@ -49,9 +53,20 @@ __global__ __launch_bounds__(256) void attn_bwd_rowdot_kernel(const uint16_t* __
   float acc = 0.f;
   if (row < rows && part * 8 < dr) {
     const int bh = row / N, n = row - bh * N;
-    const uint16_t* gp = dout + mg.head(bh, H) + (long long)n * mg.ld + part * 8;
+    const long long goff = mg.head(bh, H) + (long long)n * mg.ld + part * 8;
     const float* op = o + mo.head(bh, H) + (long long)n * mo.ld + part * 8;
-    const uint4 g = *reinterpret_cast<const uint4*>(gp);
+    uint4 g;
+    if constexpr (GRAD32) {
+      const float4 g0 = *reinterpret_cast<const float4*>(grad + goff);
+      const float4 g1 = *reinterpret_cast<const float4*>(grad + goff + 4);
+      bf16x8 r;
+      r[0] = (__bf16)g0.x, r[1] = (__bf16)g0.y, r[2] = (__bf16)g0.z, r[3] = (__bf16)g0.w;
+      r[4] = (__bf16)g1.x, r[5] = (__bf16)g1.y, r[6] = (__bf16)g1.z, r[7] = (__bf16)g1.w;
+      g = __builtin_bit_cast(uint4, r);
+      *reinterpret_cast<uint4*>(dout_w + (long long)row * dr + part * 8) = g;
+    } else {
+      g = *reinterpret_cast<const uint4*>(dout + goff);
+    }
     const float4 o0 = *reinterpret_cast<const float4*>(op);
     const float4 o1 = *reinterpret_cast<const float4*>(op + 4);
     const bf16x8 gb = as_bf16x8(g);
@@ -64,6 +79,12 @@ __global__ __launch_bounds__(256) void attn_bwd_rowdot_kernel(const uint16_t* __
     drow[row] = -acc;
     lse2[row] = lse[row] * kLog2e;
   }
+}
+
+// four consecutive outputs rounded to bf16
+__device__ __forceinline__ void store4_bf16(uint16_t* p, float a, float b, float c, float d) {
+  const bf16x2 lo = {(__bf16)a, (__bf16)b}, hi = {(__bf16)c, (__bf16)d};
+  *reinterpret_cast<uint2*>(p) = make_uint2(__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi));
 }
 
 // ------------------------------------------------------------------ dK / dV
@@ -147,7 +168,7 @@ __global__ __launch_bounds__(128 * KBW, KBW / 2) __attribute__((amdgpu_waves_per
     const uint16_t* __restrict__ dout, const float* __restrict__ drow, const float* __restrict__ lse2,
     float* __restrict__ dk, float* __restrict__ dv, uint16_t* __restrict__ ds_out, const Map mq, const Map mk,
     const Map mv, const Map mg, const Map mdk, const Map mdv, int H, int dr, int Nq, int Nk, int n_ktiles,
-    int n_whole, float c, float scale) {
+    int n_whole, float c, float scale, int out16) {
   constexpr int KK = D / 16, NCB = D / 32;
   static_assert(KS >= 1 && KS <= KK, "contraction steps within the tile");
   // operands per phase (each feeding KPW ops): first products (S or dP)
@@ -268,10 +289,11 @@ __global__ __launch_bounds__(128 * KBW, KBW / 2) __attribute__((amdgpu_waves_per
     for (int cb = 0; cb < NCB; ++cb) acc[kp][cb] = zero16();
 
   // Output row of this lane's key in block kp (dV for role P, dK for role
-  // dS) and the factor of its accumulator.
+  // dS; fp32 or bf16) and the factor of its accumulator.
   auto out_row = [&](int kp) -> float* {
     const Map& mout = role_p ? mdv : mdk;
-    return (role_p ? dv : dk) + mout.head(bh, H) + (size_t)(key0 + 32 * kp) * mout.ld;
+    const long long at = mout.head(bh, H) + (long long)(key0 + 32 * kp) * mout.ld;
+    return reinterpret_cast<float*>(reinterpret_cast<char*>(role_p ? dv : dk) + (at << (out16 ? 1 : 2)));
   };
   const float f = role_p ? 1.f : scale;
   // Whole blocks, after their last tile below mid: store the first partial
@@ -622,7 +644,9 @@ __global__ __launch_bounds__(128 * KBW, KBW / 2) __attribute__((amdgpu_waves_per
             x[e] = acc[kp][cb][4 * g + e] * f;
             pin(x[e]);  // rounded product, never fused into the add below
           }
-          if (split) {
+          if (out16) {  // bf16 rows (of one sum): half as far from the start as fp32 ones
+            store4_bf16(reinterpret_cast<uint16_t*>(out) + col, x[0], x[1], x[2], x[3]);
+          } else if (split) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) unsafeAtomicAdd(out + col + e, x[e]);
           } else if (two_part) {
@@ -675,7 +699,7 @@ __global__ __launch_bounds__(64 * NW, NW / 4) __attribute__((amdgpu_waves_per_eu
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const uint16_t* __restrict__ dout, const float* __restrict__ drow, const float* __restrict__ lse2,
     float* __restrict__ dq, const Map mq, const Map mk, const Map mv, const Map mg, const Map mdq, int H, int dr,
-    int Nq, int Nk, int n_qtiles, int total, float c, float scale, int accumulate) {
+    int Nq, int Nk, int n_qtiles, int total, float c, float scale, int accumulate, int out16) {
   constexpr int BM = 32 * NW;
   constexpr int BN = 32;
   constexpr int KK = D / 16, NCB = D / 32;
@@ -890,7 +914,18 @@ __global__ __launch_bounds__(64 * NW, NW / 4) __attribute__((amdgpu_waves_per_eu
   stage(S5{}, F{}, sb, sa, j + 5);
   wait_vmem();  // requests past the last tile must land before this LDS is reassigned
 
-  if (qrow < Nq) {
+  if (qrow < Nq && out16) {  // bf16 rows
+    uint16_t* row = reinterpret_cast<uint16_t*>(dq) + mdq.head(bh, H) + (size_t)qrow * mdq.ld;
+#pragma unroll
+    for (int cb = 0; cb < NCB; ++cb)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const int col = 32 * cb + 8 * g + 4 * h;
+        if (col < dr)
+          store4_bf16(row + col, dqacc[cb][4 * g] * scale, dqacc[cb][4 * g + 1] * scale, dqacc[cb][4 * g + 2] * scale,
+                      dqacc[cb][4 * g + 3] * scale);
+      }
+  } else if (qrow < Nq) {
     float* row = dq + mdq.head(bh, H) + (size_t)qrow * mdq.ld;
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb)
@@ -1087,13 +1122,19 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_bwd_dq_ds_kernel(
 
 // ------------------------------------------------------------------ launch
 
-template <int LPR>
-static hipError_t rowdot_l(const BwdArgs& a) {
+template <int LPR, bool GRAD32>
+static hipError_t rowdot_k(const BwdArgs& a) {
   const int rows = a.BH * a.Nq;
   constexpr int rows_per_block = 256 / LPR;
-  hipLaunchKernelGGL(attn_bwd_rowdot_kernel<LPR>, dim3((unsigned)((rows + rows_per_block - 1) / rows_per_block)),
-                     dim3(256), 0, a.stream, a.dout, a.o, a.lse, a.drow, a.lse2, a.mg, a.mo, a.H, a.Nq, a.d, rows);
+  hipLaunchKernelGGL((attn_bwd_rowdot_kernel<LPR, GRAD32>),
+                     dim3((unsigned)((rows + rows_per_block - 1) / rows_per_block)), dim3(256), 0, a.stream, a.dout,
+                     a.grad, a.dout_w, a.o, a.lse, a.drow, a.lse2, GRAD32 ? a.mgrad : a.mg, a.mo, a.H, a.Nq, a.d,
+                     rows);
   return hipGetLastError();
+}
+template <int LPR>
+static hipError_t rowdot_l(const BwdArgs& a) {
+  return a.grad != nullptr ? rowdot_k<LPR, true>(a) : rowdot_k<LPR, false>(a);
 }
 
 // Workgroups of the dK/dV kernel resident on the current device at once.
@@ -1121,7 +1162,7 @@ static hipError_t dkdv_s(const BwdArgs& a) {
   const int grid = n_whole + 2 * (total - n_whole);
   hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, STORE_DS, KBW, KPW, KS>), dim3(grid), dim3(64 * 2 * KBW), 0, a.stream, a.q,
                      a.k, a.v, a.dout, a.drow, a.lse2, a.dk, a.dv, a.ds, a.mq, a.mk, a.mv, a.mg, a.mdk, a.mdv, a.H,
-                     a.d, a.Nq, a.Nk, n_kt, n_whole, a.scale * kLog2e, a.scale);
+                     a.d, a.Nq, a.Nk, n_kt, n_whole, a.scale * kLog2e, a.scale, a.kv16 ? 1 : 0);
   return hipGetLastError();
 }
 
@@ -1185,7 +1226,7 @@ static hipError_t dkdv_d(const BwdArgs& a) {
       const uint16_t* __restrict__, const uint16_t* __restrict__, const uint16_t* __restrict__,               \
       const uint16_t* __restrict__, const float* __restrict__, const float* __restrict__, float* __restrict__, \
       float* __restrict__, uint16_t* __restrict__, const Map, const Map, const Map, const Map, const Map,      \
-      const Map, int, int, int, int, int, int, float, float);
+      const Map, int, int, int, int, int, int, float, float, int);
 VITATTN_DKDV_INSTANTIATE(128, false, 4, 1, 8)
 VITATTN_DKDV_INSTANTIATE(64, false, 4, 2, 4)
 VITATTN_DKDV_INSTANTIATE(64, false, 4, 1, 4)
@@ -1237,7 +1278,7 @@ static hipError_t dq_v(const BwdArgs& a) {
   const int total = a.BH * n_qt;
   hipLaunchKernelGGL((attn_bwd_dq_kernel<D, NW, KS>), dim3(total), dim3(64 * NW), 0, a.stream, a.q, a.k, a.v, a.dout,
                      a.drow, a.lse2, a.dq, a.mq, a.mk, a.mv, a.mg, a.mdq, a.H, a.d, a.Nq, a.Nk, n_qt, total,
-                     a.scale * kLog2e, a.scale, a.accumulate_dq ? 1 : 0);
+                     a.scale * kLog2e, a.scale, a.accumulate_dq ? 1 : 0, a.dq16 ? 1 : 0);
   return hipGetLastError();
 }
 
@@ -1245,7 +1286,7 @@ static hipError_t dq_v(const BwdArgs& a) {
   template __global__ void attn_bwd_dq_kernel<D, NW, KS>(                                                     \
       const uint16_t* __restrict__, const uint16_t* __restrict__, const uint16_t* __restrict__,               \
       const uint16_t* __restrict__, const float* __restrict__, const float* __restrict__, float* __restrict__, \
-      const Map, const Map, const Map, const Map, const Map, int, int, int, int, int, int, float, float, int);
+      const Map, const Map, const Map, const Map, const Map, int, int, int, int, int, int, float, float, int, int);
 VITATTN_DQ_INSTANTIATE(128, 8, 8)
 VITATTN_DQ_INSTANTIATE(128, 4, 8)
 VITATTN_DQ_INSTANTIATE(64, 8, 4)
@@ -1318,6 +1359,8 @@ hipError_t launch_bwd_dq(const BwdArgs& a) {
     default: return dq_d<160, 10>(a);
   }
 }
+
+bool dkdv_one_sum(int Nq) { return dkdv_mid((Nq + kDkvBQ - 1) / kDkvBQ) == 0; }
 
 hipError_t launch_bwd(const BwdArgs& a) {
   hipError_t e = launch_bwd_rowdot(a);

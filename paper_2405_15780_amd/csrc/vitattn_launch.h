@@ -98,6 +98,12 @@ struct BwdArgs {
   int H, BH, Nq, Nk, d;  // query rows and key rows per (b, h); d the head dim
   float scale;
   bool accumulate_dq;  // dq += this call's dQ instead of dq = ...
+  // training step: an fp32 upstream gradient, which the row-dot pass rounds
+  // into dout_w (= dout, dense), and bf16 outputs
+  const float* grad;
+  Map mgrad;
+  uint16_t* dout_w;
+  bool dq16, kv16;  // dq, and dk and dv (only where dkdv_one_sum), are bf16
   hipStream_t stream;
 };
 
@@ -129,6 +135,7 @@ hipError_t launch_bwd_rowdot(const BwdArgs& a);
 hipError_t launch_bwd_dkdv(const BwdArgs& a);
 hipError_t launch_bwd_dq(const BwdArgs& a);  // dQ from stored dS when a.ds is set
 hipError_t launch_bwd(const BwdArgs& a);
+bool dkdv_one_sum(int Nq);  // every key block sums its query tiles as one sum (never as two added in memory)
 hipError_t launch_merge(const MergeArgs& a);
 
 // Ulysses layout copies (see vitattn_ulysses.hip for the row orders)
