@@ -275,8 +275,8 @@ def bwd_train(q, k, v, o, lse, grad, scale=None):
     s = grad.stride()
     if not (grad.is_cuda and grad.device == q.device and grad.dtype == torch.float32 and grad.shape == q.shape
             and s[3] == 1 and s[2] >= grad.shape[3] and all(x >= 0 and x % 4 == 0 for x in s[:3])
-            and grad.data_ptr() % 16 == 0):
-        return None
+            and (grad.shape[2] + 256) * s[2] * 2 <= 0x7fffffff and grad.data_ptr() % 16 == 0):
+        return None  # (the pitch bound is the bf16 operands': past it the conversion lays the rows out anew)
     lib = library()
     dout, dq = (torch.empty((B, H, Nq, d), dtype=torch.bfloat16, device=q.device) for _ in range(2))
     kv_type = torch.bfloat16 if lib.vitattn_bwd_train_bf16_kv(Nq) else torch.float32

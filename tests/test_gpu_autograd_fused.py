@@ -75,3 +75,16 @@ def test_both_sides_of_the_two_sum_limit(Nq, Nk):
     g = t.Generator(device="cuda").manual_seed(7500)
     q, k, v = (t.randn((B, H, n, d), generator=g, device="cuda").bfloat16() for n in (Nq, Nk, Nk))
     check(q, k, v, grads(t, "bnhd", (B, H, Nq, d)), 0.125)
+
+
+def test_gradient_row_pitch_past_31_bits():
+    # rows 2^31 elements apart (heads between them): more than the library's pitch limit, so converted first
+    t = torch()
+    B, H, N, d = 1, 2, 2, 64
+    print("case fused conversions, row pitch 2^31", flush=True)
+    x = workloads.make_small_inputs(B, H, N, d, seed=7600)
+    q, k, v = (to_device(x[n]) for n in ("q", "k", "v"))
+    pitch = 1 << 31
+    g = t.empty(pitch + H * d, dtype=t.float32, device="cuda").as_strided((B, H, N, d), (H * d, d, pitch, 1))
+    g.copy_(grads(t, "dense", (B, H, N, d)))
+    check(q, k, v, g, 0.125)
