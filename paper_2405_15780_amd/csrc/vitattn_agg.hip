@@ -94,6 +94,19 @@ __device__ __forceinline__ void load_chunks(const uint16_t* p, const bool (&ok)[
   for (int u = 0; u < G; ++u) x[u] = ok[u] ? load16(p + (size_t)u * 512) : make_uint4(0u, 0u, 0u, 0u);
 }
 
+// the four bf16 values of an 8-byte piece
+__device__ __forceinline__ void widen4(uint2 x, float (&y)[4]) {
+  y[0] = __uint_as_float(x.x << 16), y[1] = __uint_as_float(x.x & 0xffff0000u);
+  y[2] = __uint_as_float(x.y << 16), y[3] = __uint_as_float(x.y & 0xffff0000u);
+}
+
+// four outputs that are not read again here, written past the caches
+__device__ __forceinline__ void store4_stream(float* p, float a, float b, float c, float d) {
+  typedef float f4 __attribute__((ext_vector_type(4)));
+  const f4 x = {a, b, c, d};
+  __builtin_nontemporal_store(x, reinterpret_cast<f4*>(p));
+}
+
 __device__ __forceinline__ void store8(float* p, const float (&x)[8]) {
   reinterpret_cast<float4*>(p)[0] = make_float4(x[0], x[1], x[2], x[3]);
   reinterpret_cast<float4*>(p)[1] = make_float4(x[4], x[5], x[6], x[7]);
@@ -199,6 +212,20 @@ __global__ __launch_bounds__(256) void attn_agg_bwd_kernel(
     const size_t base = inst * C * D + lane * 8;
     float g[8], ox[8];
     widen8(load16(dout + inst * D + cg * 8), g);
+    // Bound by its stores (dK and dV are twice the bytes read). A row of dK is
+    // ds_c times q and one of dV p_c times dout, so any lane can form any
+    // element from the row's two numbers: each takes the four columns that make
+    // a wave's store 1 KB of consecutive bytes, half a chunk, and fetches the
+    // numbers from the row's first lane. Storing the eight columns a lane
+    // loads wrote every other 16 bytes per instruction. The stores are
+    // streamed. Forward + backward, M=8,192, H=16, d=64: C=92 2,343 -> 2,303
+    // us, C=33 824 -> 763, C=24 647 -> 578; M=2,000, C=8 66 -> 53 (without
+    // streaming 2,333, 811, 626 and 63). Same products, same bits.
+    const int srow = 4 * lane / D, scol = 4 * lane % D;
+    const size_t sbase = inst * C * D + 4 * lane;
+    float sq[4], sg[4];
+    widen4(*reinterpret_cast<const uint2*>(q + (size_t)h * D + scol), sq);
+    widen4(*reinterpret_cast<const uint2*>(dout + inst * D + scol), sg);
     const float4 o0 = reinterpret_cast<const float4*>(o + inst * D + cg * 8)[0];
     const float4 o1 = reinterpret_cast<const float4*>(o + inst * D + cg * 8)[1];
     ox[0] = o0.x, ox[1] = o0.y, ox[2] = o0.z, ox[3] = o0.w, ox[4] = o1.x, ox[5] = o1.y, ox[6] = o1.z, ox[7] = o1.w;
@@ -222,16 +249,16 @@ __global__ __launch_bounds__(256) void attn_agg_bwd_kernel(
         // rows past C (zeros) must add nothing, whatever exp2 gives there
         const float p = ok[u] ? exp2f(s * c2 - l2) : 0.f;
         const float ds = ok[u] ? p * (dp - Dm) : 0.f;
-        if (ok[u]) {
-          const float f = scale * ds;
-          float dkx[8], dvx[8];
+        const float f = scale * ds;
 #pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            dkx[e] = f * qv[e];
-            dvx[e] = p * g[e];
+        for (int j = 0; j < 2; ++j) {
+          const int row = 256 / D * j + srow;
+          const float fr = __shfl(f, row * LPR), pr = __shfl(p, row * LPR);
+          if ((t0 + u) * RPC + row < C) {
+            const size_t at = sbase + (size_t)(t0 + u) * 512 + 256 * j;
+            store4_stream(dk + at, fr * sq[0], fr * sq[1], fr * sq[2], fr * sq[3]);
+            store4_stream(dv + at, pr * sg[0], pr * sg[1], pr * sg[2], pr * sg[3]);
           }
-          store8(dk + base + (size_t)(t0 + u) * 512, dkx);
-          store8(dv + base + (size_t)(t0 + u) * 512, dvx);
         }
 #pragma unroll
         for (int e = 0; e < 8; ++e) dqa[e] = fmaf(ds, kx[e], dqa[e]);
@@ -304,8 +331,8 @@ int agg_partials(int M) { return (M + 3) / 4; }
 // C=8 (one chunk) forward 37.1 -> 16.9 us, backward 87 -> 39 us; M=8,192, C=24
 // (three) 184 -> 132 us and 495 -> 477 us. The backward takes groups of 12
 // from five chunks on: with smaller ones more waves are in flight and their
-// stores come between other waves' loads (M=8,192, H=16, C=33: 605 us in groups
-// of 12, 651 in groups of 6).
+// stores come between other waves' loads (M=8,192, H=16, C=33: 605 us in
+// groups of 12, 651 in groups of 6, both before the stores were streamed).
 static int agg_group(int C, int d) {
   const int chunks = (C + 512 / d - 1) / (512 / d);
   const int groups = (chunks + kAggChunkGroup - 1) / kAggChunkGroup;
