@@ -275,8 +275,12 @@ def bwd_train(q, k, v, o, lse, grad, scale=None):
     s = grad.stride()
     if not (grad.is_cuda and grad.device == q.device and grad.dtype == torch.float32 and grad.shape == q.shape
             and s[3] == 1 and s[2] >= grad.shape[3] and all(x >= 0 and x % 4 == 0 for x in s[:3])
-            and (grad.shape[2] + 256) * s[2] * 2 <= 0x7fffffff and grad.data_ptr() % 16 == 0):
-        return None  # (the pitch bound is the bf16 operands': past it the conversion lays the rows out anew)
+            and (grad.shape[2] + 256) * s[2] * 2 <= 0x7fffffff and not grad.is_neg() and grad.data_ptr() != 0
+            and grad.data_ptr() % 16 == 0):
+        # The pitch bound is the bf16 operands': past it the conversion lays the
+        # rows out anew. It also negates a lazily negated view (the memory holds
+        # the opposite signs) and fills in zeros that have no memory yet.
+        return None
     lib = library()
     dout, dq = (torch.empty((B, H, Nq, d), dtype=torch.bfloat16, device=q.device) for _ in range(2))
     kv_type = torch.bfloat16 if lib.vitattn_bwd_train_bf16_kv(Nq) else torch.float32

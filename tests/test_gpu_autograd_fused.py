@@ -88,3 +88,20 @@ def test_gradient_row_pitch_past_31_bits():
     g = t.empty(pitch + H * d, dtype=t.float32, device="cuda").as_strided((B, H, N, d), (H * d, d, pitch, 1))
     g.copy_(grads(t, "dense", (B, H, N, d)))
     check(q, k, v, g, 0.125)
+
+
+@pytest.mark.parametrize("kind", ["negated view", "zeros without memory"])
+def test_gradients_whose_memory_is_not_their_values(kind):
+    # a lazily negated view holds the opposite signs, a lazy zero tensor no memory at all
+    t = torch()
+    B, H, N, d = 1, 2, 97, 64
+    print(f"case fused conversions {kind}", flush=True)
+    x = workloads.make_small_inputs(B, H, N, d, seed=7700)
+    q, k, v = (to_device(x[n]) for n in ("q", "k", "v"))
+    if kind == "negated view":
+        g = t._neg_view(grads(t, "dense", (B, H, N, d)))
+        assert g.is_neg() and g.is_contiguous()
+    else:
+        g = t._efficientzerotensor((B, H, N, d), device="cuda")
+        assert g.data_ptr() == 0
+    check(q, k, v, g, 0.125)
