@@ -247,7 +247,8 @@ int vitattn_bwd_strided(const void* q, vitattn_strides sq, const void* k, vitatt
  * the place of vitattn_bwd's dout. dq is written as bf16 [B][H][Nq][d], dk and
  * dv as bf16 [B][H][Nk][d] where vitattn_bwd_train_bf16_kv(Nq) is 1 and as
  * fp32 otherwise, all dense. The values are those of the separate conversions
- * (round to nearest even), bit for bit. dout must not alias grad. The other
+ * (round to nearest even), bit for bit. dout must not alias grad
+ * (dout == grad is rejected; partial overlap is not detected). The other
  * arguments, the validation and the status are vitattn_bwd_strided's.
  */
 int vitattn_bwd_train_bf16_kv(int Nq);

@@ -300,7 +300,7 @@ int vitattn_bwd_train(const void* q, vitattn_strides sq, const void* k, vitattn_
     if (st != VITATTN_OK) return st;
     if (!bwd_items_ok(B, H, Nq, Nk, d)) return VITATTN_E_INVAL;
     if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(o) || !aligned16(grad) || !aligned16(lse) ||
-        !aligned16(dout) || !aligned16(dq) || !aligned16(dk) || !aligned16(dv))
+        !aligned16(dout) || !aligned16(dq) || !aligned16(dk) || !aligned16(dv) || dout == grad)
       return VITATTN_E_INVAL;
     if (!scale_ok(scale)) return VITATTN_E_INVAL;
     if (check_map(sq, B, H, Nq, d, 2, false) || check_map(sk, B, H, Nk, d, 2, false) ||

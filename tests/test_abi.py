@@ -374,6 +374,67 @@ def test_bwd_strided_output_overlap_and_workspace():
     assert b.untouched()
 
 
+# ------------------------------------------------------------ training step
+
+
+def bwd_train(b, B=2, H=2, Nq=8, Nk=8, d=72, scale=0.125, ptr=None, layout=None, ws="ws", ws_bytes=None):
+    """ptr: {index: address} over q k v o grad lse dout dq dk dv; layout: {index: strides} over q k v o grad."""
+    p = [b.p(i) for i in range(10)]
+    for i, val in (ptr or {}).items():
+        p[i] = val
+    st = [S(H * n * d, n * d, d) for n in (Nq, Nk, Nk, Nq, Nq)]
+    for i, val in (layout or {}).items():
+        st[i] = val
+    wsb = va.workspace_bytes(2, 2, 8, 72) if ws_bytes is None else ws_bytes
+    return lib().vitattn_bwd_train(p[0], st[0], p[1], st[1], p[2], st[2], p[3], st[3], p[4], st[4], p[5], p[6], p[7],
+                                   p[8], p[9], B, H, Nq, Nk, d, scale, b.p(10) if ws == "ws" else ws, wsb, None)
+
+
+@pytest.mark.parametrize("which", range(10))
+def test_bwd_train_rejects_null_and_misaligned_pointers(which):
+    b = Bufs()
+    assert bwd_train(b, ptr={which: None}) == E_INVAL
+    assert bwd_train(b, ptr={which: b.p(which) + 8}) == E_INVAL
+    assert b.untouched()
+
+
+@pytest.mark.parametrize("which", range(5))
+def test_bwd_train_rejects_a_bad_layout_on_any_operand(which):
+    b = Bufs()
+    unit = 8 if which < 3 else 4  # elements of 16 bytes: q, k, v are bf16, o and grad fp32
+    for bad in (S(1152, 576, 64), S(1152, 576, 72 + unit // 2), S(1152, 576 + unit // 2, 72),
+                S(1152 + unit // 2, 576, 72), S(1152, -576, 72), S(1152, 576, 1 << 31)):
+        assert bwd_train(b, layout={which: bad}) == E_INVAL, (bad.batch, bad.head, bad.row)
+    assert b.untouched()
+
+
+@pytest.mark.parametrize("kw,expected", [
+    (dict(B=0), E_INVAL), (dict(H=0), E_INVAL), (dict(Nq=0), E_INVAL), (dict(Nk=0), E_INVAL),
+    (dict(d=100), E_UNSUP), (dict(d=168), E_UNSUP), (dict(scale=0.0), E_INVAL), (dict(scale=float("nan")), E_INVAL),
+    (dict(B=65536, H=65536), E_INVAL), (dict(B=2, H=2_800_000, Nq=1, d=8), E_INVAL),
+    (dict(ws_bytes=511), E_WS), (dict(ws=None), E_WS),
+    (dict(ws_bytes=va.workspace_bytes(2, 2, 8, 72) - 1), E_WS),
+])
+def test_bwd_train_rejects_bad_arguments(kw, expected):
+    b = Bufs()
+    assert bwd_train(b, **kw) == expected
+    assert b.untouched()
+
+
+def test_bwd_train_rejects_a_misaligned_workspace_and_rounding_in_place():
+    b = Bufs()
+    assert bwd_train(b, ws=b.p(10) + 8) == E_WS
+    # grad rounded into its own memory: rows of dout would overwrite rows of grad still to be read
+    assert bwd_train(b, ptr={6: b.p(4)}) == E_INVAL
+    assert b.untouched()
+
+
+def test_bwd_train_output_type_of_dk_and_dv_by_query_count():
+    kv16 = lib().vitattn_bwd_train_bf16_kv
+    assert [kv16(n) for n in (1, 16320, 16321, 188416)] == [1, 1, 0, 0]  # 255 query tiles of 64, 256
+    assert kv16(0) == 0 and kv16(-5) == 0
+
+
 # ------------------------------------------------------------ dS mode
 
 
