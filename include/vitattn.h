@@ -257,6 +257,22 @@ int vitattn_bwd_train(const void* q, vitattn_strides sq, const void* k, vitattn_
                       const float* lse, void* dout, void* dq, void* dk, void* dv, int B, int H, int Nq, int Nk, int d,
                       float scale, void* workspace, size_t workspace_bytes, void* stream);
 
+/*
+ * Which forms of the kernels a call of these sizes takes on the current
+ * device (flags as in vitattn_bwd_kv): the results do not depend on them, so
+ * this serves tests and the reading of profiles. Launches nothing and needs no
+ * GPU; without one it gives the forms of a device that tells nothing about
+ * itself.
+ *   fwd_waves, dq_waves : waves per workgroup, 32 query rows each
+ *   dkdv_keys           : keys per dK/dV workgroup
+ *   dkdv_whole          : key blocks (of that many keys) with one workgroup
+ *   dkdv_split          : key blocks split over two workgroups
+ */
+typedef struct vitattn_forms {
+  int fwd_waves, dq_waves, dkdv_keys, dkdv_whole, dkdv_split;
+} vitattn_forms;
+int vitattn_launch_forms(int B, int H, int Nq, int Nk, int d, int flags, vitattn_forms* forms);
+
 /* The two kernels of the dS mode as separate calls (dense operands, Nq = Nk =
  * N; the row-statistics stage vitattn_bwd_rowdot runs first), for timing each:
  * vitattn_bwd_dkdv_ds writes dK, dV and the dS blocks into the workspace,

@@ -25,6 +25,11 @@ class Strides(ctypes.Structure):
     _fields_ = [("batch", ctypes.c_longlong), ("head", ctypes.c_longlong), ("row", ctypes.c_longlong)]
 
 
+class Forms(ctypes.Structure):
+    """vitattn_forms: the kernel forms a call takes."""
+    _fields_ = [(n, ctypes.c_int) for n in ("fwd_waves", "dq_waves", "dkdv_keys", "dkdv_whole", "dkdv_split")]
+
+
 _S = Strides
 
 _SIGNATURES = {
@@ -45,6 +50,7 @@ _SIGNATURES = {
     "vitattn_bwd_train_bf16_kv": (c_int, [c_int]),
     "vitattn_bwd_train": (c_int, [c_void_p, _S] * 5 + [c_void_p] * 5 + [c_int] * 5
                           + [c_float, c_void_p, c_size_t, c_void_p]),
+    "vitattn_launch_forms": (c_int, [c_int] * 6 + [ctypes.POINTER(Forms)]),
     "vitattn_merge": (c_int, [c_void_p] * 2 + [c_int] + [c_void_p] * 2 + [c_int] * 4 + [c_void_p]),
     "vitattn_agg_fwd": (c_int, [c_void_p] * 5 + [c_int] * 4 + [c_float, c_void_p]),
     "vitattn_agg_bwd_workspace_bytes": (c_size_t, [c_int] * 4),
@@ -291,6 +297,13 @@ def bwd_train(q, k, v, o, lse, grad, scale=None):
                                  lse.data_ptr(), dout.data_ptr(), dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), B, H,
                                  Nq, Nk, d, _default_scale(d, scale), ws.data_ptr(), ws_bytes, _stream_ptr(q)))
     return dq, dk.to(torch.bfloat16), dv.to(torch.bfloat16)
+
+
+def launch_forms(B, H, Nq, Nk, d, flags=0):
+    """The kernel forms (a Forms) that calls of these sizes take on the current device."""
+    forms = Forms()
+    _check(library().vitattn_launch_forms(B, H, Nq, Nk, d, flags, ctypes.byref(forms)))
+    return forms
 
 
 VITATTN_NOALLOC_MAX_ROWS = 4194304

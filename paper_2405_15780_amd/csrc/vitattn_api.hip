@@ -326,6 +326,27 @@ int vitattn_bwd_train(const void* q, vitattn_strides sq, const void* k, vitattn_
   }
 }
 
+int vitattn_launch_forms(int B, int H, int Nq, int Nk, int d, int flags, vitattn_forms* forms) {
+  try {
+    const int st = check_sizes_kv(B, H, Nq, Nk, d);
+    if (st != VITATTN_OK) return st;
+    if (!bwd_items_ok(B, H, Nq, Nk, d) || forms == nullptr) return VITATTN_E_INVAL;
+    if ((flags & ~(VITATTN_BWD_ACCUMULATE_DQ | VITATTN_BWD_STORE_DS)) != 0) return VITATTN_E_INVAL;
+    vitattn::FwdArgs f = {};  // the rules read the sizes alone
+    vitattn::BwdArgs a = {};
+    f.BH = a.BH = B * H;
+    f.Nq = a.Nq = Nq;
+    f.Nk = a.Nk = Nk;
+    f.d = a.d = d;
+    if (flags & VITATTN_BWD_STORE_DS) a.ds = reinterpret_cast<uint16_t*>(16);  // selects the mode; never accessed
+    const vitattn::BwdForms b = vitattn::bwd_forms(a);
+    *forms = {vitattn::fwd_waves(f), b.dq_waves, b.dkdv_keys, b.dkdv_whole, b.dkdv_split};
+    return VITATTN_OK;
+  } catch (...) {
+    return VITATTN_E_INTERNAL;
+  }
+}
+
 int vitattn_merge(const float* o_parts, const float* lse_parts, int n_parts, float* o, float* lse, int B, int H,
                   int N, int d, void* stream) {
   try {

@@ -1144,45 +1144,47 @@ static Resident dkdv_resident() {
   return cache.get(reinterpret_cast<const void*>(attn_bwd_dkdv_kernel<D, STORE_DS, KBW, KPW, KS>), 128 * KBW);
 }
 
-template <int D, bool STORE_DS, int KBW, int KPW, int KS = D / 16>
-static hipError_t dkdv_s(const BwdArgs& a) {
-  constexpr int BK = 32 * KBW * KPW;
-  const int n_kt = (a.Nk + BK - 1) / BK;
-  const int total = a.BH * n_kt;
-  // A last round at most half full is split in two halves of the query range
-  // (when the key blocks take two sums), so that it takes half as long.
-  const int slots = dkdv_resident<D, STORE_DS, KBW, KPW, KS>().workgroups;
-  const int tail = slots > 0 ? total % slots : 0;
-  int n_whole = total;
-  if (tail > 0 && 2 * tail <= slots && dkdv_mid((a.Nq + kDkvBQ - 1) / kDkvBQ) > 0) {
-    n_whole = total - tail;
-    hipLaunchKernelGGL(zero_key_blocks_kernel, dim3(2 * tail), dim3(256), 0, a.stream, a.dk, a.dv, a.mdk, a.mdv, a.H,
-                       a.d, a.Nk, n_kt, n_whole, BK);
-  }
-  const int grid = n_whole + 2 * (total - n_whole);
-  hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, STORE_DS, KBW, KPW, KS>), dim3(grid), dim3(64 * 2 * KBW), 0, a.stream, a.q,
-                     a.k, a.v, a.dout, a.drow, a.lse2, a.dk, a.dv, a.ds, a.mq, a.mk, a.mv, a.mg, a.mdk, a.mdv, a.H,
-                     a.d, a.Nq, a.Nk, n_kt, n_whole, a.scale * kLog2e, a.scale, a.kv16 ? 1 : 0);
-  return hipGetLastError();
-}
+// How a dK/dV launch covers its key blocks: `keys` per workgroup, n_kt key
+// blocks per (b, h), the first n_whole of them one workgroup each and n_split
+// more in two halves each. cost: its estimated time, in rounds of the widest
+// form.
+struct DkdvPlan {
+  int keys, n_kt, n_whole, n_split;
+  double cost;
+};
 
-// Estimated time of a dK/dV launch: whole rounds of resident workgroups, then
-// the last one, alone on its CUs or two to a CU, or split. one, two: a round's
-// time with one and with two workgroups per CU, against one of the widest form.
-static double dkdv_cost(const BwdArgs& a, int keys, const Resident& r, double one, double two) {
-  if (r.workgroups <= 0) return one;
-  const long long n = (long long)a.BH * ((a.Nk + keys - 1) / keys);
-  const long long rounds = n / r.workgroups, left = n - rounds * r.workgroups;
+// Whole rounds of resident workgroups, then the last one, alone on its CUs or
+// two to a CU, or, at most half full, split in two halves of the query range
+// (where the key blocks take two sums). one, two: a round's time with one and
+// with two workgroups per CU. Without the device's figures nothing is split
+// and the widest form wins.
+static DkdvPlan dkdv_form(const BwdArgs& a, int keys, const Resident& r, double one, double two) {
+  const int n_kt = (a.Nk + keys - 1) / keys, n = a.BH * n_kt;
+  if (r.workgroups <= 0) return {keys, n_kt, n, 0, 1. / keys};
+  const int rounds = n / r.workgroups, left = n - rounds * r.workgroups;
   const int n_qt = (a.Nq + kDkvBQ - 1) / kDkvBQ;
   const double full = r.workgroups > r.cus ? two : one;
   double last = left == 0 ? 0. : left <= r.cus ? one : full;
-  if (left > 0 && 2 * left <= r.workgroups && dkdv_mid(n_qt) > 0)
-    last = 0.5 * last + 0.8 * left / n_qt * keys * tile_width(a.d) / (128. * 128.);  // the halves' atomics
-  return rounds * full + last;
+  const bool split = left > 0 && 2 * left <= r.workgroups && dkdv_mid(n_qt) > 0;
+  if (split) last = 0.5 * last + 0.8 * left / n_qt * keys * tile_width(a.d) / (128. * 128.);  // the halves' atomics
+  return {keys, n_kt, split ? n - left : n, split ? left : 0, rounds * full + last};
+}
+static DkdvPlan cheaper(const DkdvPlan& x, const DkdvPlan& y) { return y.cost < x.cost ? y : x; }
+
+template <int D, bool STORE_DS, int KBW, int KPW, int KS>
+static hipError_t dkdv_launch(const BwdArgs& a, const DkdvPlan& p) {
+  if (p.n_split > 0)
+    hipLaunchKernelGGL(zero_key_blocks_kernel, dim3(2 * p.n_split), dim3(256), 0, a.stream, a.dk, a.dv, a.mdk, a.mdv,
+                       a.H, a.d, a.Nk, p.n_kt, p.n_whole, p.keys);
+  hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, STORE_DS, KBW, KPW, KS>), dim3(p.n_whole + 2 * p.n_split),
+                     dim3(128 * KBW), 0, a.stream, a.q, a.k, a.v, a.dout, a.drow, a.lse2, a.dk, a.dv, a.ds, a.mq, a.mk,
+                     a.mv, a.mg, a.mdk, a.mdv, a.H, a.d, a.Nq, a.Nk, p.n_kt, p.n_whole, a.scale * kLog2e, a.scale,
+                     a.kv16 ? 1 : 0);
+  return hipGetLastError();
 }
 
 // The widest form at the narrowest tile in the recompute mode: each wave holds
-// two 32-key blocks (220 VGPRs, two waves per SIMD, 256 keys per workgroup),
+// two 32-key blocks (226 VGPRs, two waves per SIMD, 256 keys per workgroup),
 // so every operand it reads from LDS feeds two matrix-core ops and every Q /
 // dO tile it streams serves twice the keys: 8 % faster than six one-block
 // pairs at three waves per SIMD (B=4, H=1, N=188,416, d=64), with the same
@@ -1190,7 +1192,7 @@ static double dkdv_cost(const BwdArgs& a, int keys, const Resident& r, double on
 // SIMD only, which measured 5 % slower at d=128 and no faster at d=96. In the
 // 96-wide tile a head dim up to 80 contracts S and dP over five 16-column
 // steps instead of six, and the recompute mode then fits three waves per SIMD
-// (166 VGPRs): six pairs, 192 keys per workgroup, 4-5 % faster at d=72 on large grids, with
+// (168 VGPRs): six pairs, 192 keys per workgroup, 4-5 % faster at d=72 on large grids, with
 // the same bits. The dS mode keeps four pairs of one-block waves (its stored
 // dS blocks are laid out per 128 keys).
 // Narrower forms (fewer keys per workgroup, the same ops per key block) run
@@ -1200,25 +1202,28 @@ static double dkdv_cost(const BwdArgs& a, int keys, const Resident& r, double on
 // CU; d <= 80 four pairs 0.79, two pairs 0.52; else two pairs 0.62-0.67.
 // H=2, N=8,191, d=128: 310 -> 157 us; H=1, N=4,096, d=64: 99 -> 51 us.
 template <int D, int KS>
-static hipError_t dkdv_d(const BwdArgs& a) {
-  if (a.ds != nullptr) return dkdv_s<D, true, 4, 1, KS>(a);
+static DkdvPlan dkdv_plan(const BwdArgs& a) {
+  if (a.ds != nullptr) return dkdv_form(a, 128, dkdv_resident<D, true, 4, 1, KS>(), 1., 1.);
+  const Resident r4 = dkdv_resident<D, false, 4, 1, KS>(), r2 = dkdv_resident<D, false, 2, 1, KS>();
   if constexpr (D == 64) {
-    const double wide = dkdv_cost(a, 256, dkdv_resident<D, false, 4, 2, KS>(), 1., 1.);
-    const double four = dkdv_cost(a, 128, dkdv_resident<D, false, 4, 1, KS>(), 0.59, 0.59);
-    const double two = dkdv_cost(a, 64, dkdv_resident<D, false, 2, 1, KS>(), 0.4, 0.61);
-    if (two < four && two < wide) return dkdv_s<D, false, 2, 1, KS>(a);
-    return four < wide ? dkdv_s<D, false, 4, 1, KS>(a) : dkdv_s<D, false, 4, 2, KS>(a);
+    const DkdvPlan wide = dkdv_form(a, 256, dkdv_resident<D, false, 4, 2, KS>(), 1., 1.);
+    return cheaper(cheaper(wide, dkdv_form(a, 128, r4, 0.59, 0.59)), dkdv_form(a, 64, r2, 0.4, 0.61));
   } else if constexpr (KS == 5) {
-    const double wide = dkdv_cost(a, 192, dkdv_resident<D, false, 6, 1, KS>(), 1., 1.);
-    const double four = dkdv_cost(a, 128, dkdv_resident<D, false, 4, 1, KS>(), 0.79, 0.79);
-    const double two = dkdv_cost(a, 64, dkdv_resident<D, false, 2, 1, KS>(), 0.52, 0.79);
-    if (two < four && two < wide) return dkdv_s<D, false, 2, 1, KS>(a);
-    return four < wide ? dkdv_s<D, false, 4, 1, KS>(a) : dkdv_s<D, false, 6, 1, KS>(a);
+    const DkdvPlan wide = dkdv_form(a, 192, dkdv_resident<D, false, 6, 1, KS>(), 1., 1.);
+    return cheaper(cheaper(wide, dkdv_form(a, 128, r4, 0.79, 0.79)), dkdv_form(a, 64, r2, 0.52, 0.79));
   } else {
-    const double wide = dkdv_cost(a, 128, dkdv_resident<D, false, 4, 1, KS>(), 1., 1.);
-    const double two = dkdv_cost(a, 64, dkdv_resident<D, false, 2, 1, KS>(), 0.65, 1.);
-    return two < wide ? dkdv_s<D, false, 2, 1, KS>(a) : dkdv_s<D, false, 4, 1, KS>(a);
+    return cheaper(dkdv_form(a, 128, r4, 1., 1.), dkdv_form(a, 64, r2, 0.65, 1.));
   }
+}
+template <int D, int KS>
+static hipError_t dkdv_d(const BwdArgs& a) {
+  const DkdvPlan p = dkdv_plan<D, KS>(a);
+  if (a.ds != nullptr) return dkdv_launch<D, true, 4, 1, KS>(a, p);
+  if constexpr (D == 64)
+    if (p.keys == 256) return dkdv_launch<D, false, 4, 2, KS>(a, p);
+  if constexpr (KS == 5)
+    if (p.keys == 192) return dkdv_launch<D, false, 6, 1, KS>(a, p);
+  return p.keys == 128 ? dkdv_launch<D, false, 4, 1, KS>(a, p) : dkdv_launch<D, false, 2, 1, KS>(a, p);
 }
 
 #define VITATTN_DKDV_INSTANTIATE(D, S, KBW, KPW, KS)                                                           \
@@ -1313,6 +1318,14 @@ hipError_t launch_bwd_dkdv(const BwdArgs& a) {
     default: return dkdv_d<160, 10>(a);
   }
 }
+static DkdvPlan dkdv_plan_of(const BwdArgs& a) {
+  switch (tile_width(a.d)) {
+    case 64: return dkdv_plan<64, 4>(a);
+    case 96: return a.d <= 80 ? dkdv_plan<96, 5>(a) : dkdv_plan<96, 6>(a);
+    case 128: return dkdv_plan<128, 8>(a);
+    default: return dkdv_plan<160, 10>(a);
+  }
+}
 hipError_t launch_bwd_dq_ds(const BwdArgs& a) {
   switch (tile_width(a.d)) {
     case 64: return dq_ds_d<64>(a);
@@ -1340,14 +1353,30 @@ static Resident dq_resident() {
 // d=72: 29.4 -> 28.8 ms), but in coarser work items. All compute every dQ row
 // with the same operations in the same order, so the choice changes no bit.
 template <int D, int KS>
-static hipError_t dq_d(const BwdArgs& a) {
+static int dq_waves(const BwdArgs& a) {
   const double c8 = launch_cost(a.BH, a.Nq, a.Nk, 8, dq_resident<D, 8, KS>());
   const double c4 = launch_cost(a.BH, a.Nq, a.Nk, 4, dq_resident<D, 4, KS>());
   if constexpr (KS <= 5) {
     const double c12 = launch_cost(a.BH, a.Nq, a.Nk, 12, dq_resident<D, 12, KS>()) / 1.02;
-    if (c12 < c8 && c12 < c4) return dq_v<D, 12, KS>(a);
+    if (c12 < c8 && c12 < c4) return 12;
   }
-  return c4 < c8 ? dq_v<D, 4, KS>(a) : dq_v<D, 8, KS>(a);
+  return c4 < c8 ? 4 : 8;
+}
+template <int D, int KS>
+static hipError_t dq_d(const BwdArgs& a) {
+  const int nw = dq_waves<D, KS>(a);
+  if constexpr (KS <= 5)
+    if (nw == 12) return dq_v<D, 12, KS>(a);
+  return nw == 4 ? dq_v<D, 4, KS>(a) : dq_v<D, 8, KS>(a);
+}
+static int dq_waves_of(const BwdArgs& a) {
+  if (a.ds != nullptr) return 8;
+  switch (tile_width(a.d)) {
+    case 64: return dq_waves<64, 4>(a);
+    case 96: return a.d <= 80 ? dq_waves<96, 5>(a) : dq_waves<96, 6>(a);
+    case 128: return dq_waves<128, 8>(a);
+    default: return dq_waves<160, 10>(a);
+  }
 }
 
 hipError_t launch_bwd_dq(const BwdArgs& a) {
@@ -1361,6 +1390,11 @@ hipError_t launch_bwd_dq(const BwdArgs& a) {
 }
 
 bool dkdv_one_sum(int Nq) { return dkdv_mid((Nq + kDkvBQ - 1) / kDkvBQ) == 0; }
+
+BwdForms bwd_forms(const BwdArgs& a) {
+  const DkdvPlan p = dkdv_plan_of(a);
+  return {p.keys, p.n_whole, p.n_split, dq_waves_of(a)};
+}
 
 hipError_t launch_bwd(const BwdArgs& a) {
   hipError_t e = launch_bwd_rowdot(a);

@@ -358,7 +358,9 @@ static Resident fwd_resident() {
   return cache.get(reinterpret_cast<const void*>(attn_fwd_kernel<D, KB, NW, MINW, KS>), 64 * NW);
 }
 
-// Waves per workgroup, by the shorter estimated time (launch_cost below). A
+constexpr int fwd_minw4(int D) { return D == 64 ? 3 : 2; }  // waves per SIMD that four-wave workgroups make room for
+
+// Waves per workgroup, by the shorter estimated time (launch_cost). A
 // workgroup of 4 waves (128 queries) has a CU's SIMDs to itself while the
 // grid leaves others idle: one alone on a CU takes 0.72-0.83 of the time of
 // 8 waves on it, two 1.02-1.05, three (d <= 64) 1.48 (measured at N = 16,384,
@@ -373,15 +375,21 @@ static Resident fwd_resident() {
 // coarser work items. Each query row is computed by the same operations in
 // the same order in all of them, so the choice changes no bit.
 template <int D, int KB, int KS>
-static hipError_t launch_fwd_d(const FwdArgs& a) {
-  constexpr int MINW4 = D == 64 ? 3 : 2;
-  const Resident r8 = fwd_resident<D, KB, 8, 2, KS>(), r4 = fwd_resident<D, KB, 4, MINW4, KS>();
+static int fwd_waves_d(const FwdArgs& a) {
+  const Resident r8 = fwd_resident<D, KB, 8, 2, KS>(), r4 = fwd_resident<D, KB, 4, fwd_minw4(D), KS>();
   const double c8 = launch_cost(a.BH, a.Nq, a.Nk, 8, r8), c4 = launch_cost(a.BH, a.Nq, a.Nk, 4, r4);
   if constexpr (D == 64) {
     const double c12 = launch_cost(a.BH, a.Nq, a.Nk, 12, fwd_resident<D, KB, 12, 3, KS>()) / 1.05;
-    if (c12 < c8 && c12 < c4) return launch_fwd_v<D, KB, 12, 3, KS>(a);
+    if (c12 < c8 && c12 < c4) return 12;
   }
-  return c4 < c8 ? launch_fwd_v<D, KB, 4, MINW4, KS>(a) : launch_fwd_v<D, KB, 8, 2, KS>(a);
+  return c4 < c8 ? 4 : 8;
+}
+template <int D, int KB, int KS>
+static hipError_t launch_fwd_d(const FwdArgs& a) {
+  const int nw = fwd_waves_d<D, KB, KS>(a);
+  if constexpr (D == 64)
+    if (nw == 12) return launch_fwd_v<D, KB, 12, 3, KS>(a);
+  return nw == 4 ? launch_fwd_v<D, KB, 4, fwd_minw4(D), KS>(a) : launch_fwd_v<D, KB, 8, 2, KS>(a);
 }
 
 // Tile shape per width: two 32-key blocks per tile, except at D = 160, where
@@ -394,6 +402,15 @@ hipError_t launch_fwd(const FwdArgs& a) {
     case 96: return a.d <= 80 ? launch_fwd_d<96, 2, 5>(a) : launch_fwd_d<96, 2, 6>(a);
     case 128: return launch_fwd_d<128, 2, 8>(a);
     default: return launch_fwd_d<160, 1, 10>(a);
+  }
+}
+
+int fwd_waves(const FwdArgs& a) {
+  switch (tile_width(a.d)) {
+    case 64: return fwd_waves_d<64, 2, 4>(a);
+    case 96: return a.d <= 80 ? fwd_waves_d<96, 2, 5>(a) : fwd_waves_d<96, 2, 6>(a);
+    case 128: return fwd_waves_d<128, 2, 8>(a);
+    default: return fwd_waves_d<160, 1, 10>(a);
   }
 }
 

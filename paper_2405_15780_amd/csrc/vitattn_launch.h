@@ -117,6 +117,7 @@ struct MergeArgs {
 };
 
 hipError_t launch_fwd(const FwdArgs& a);
+int fwd_waves(const FwdArgs& a);  // waves per workgroup of the forward that launch_fwd takes
 
 // Workspace layout of the backward pass: two fp32 regions of region_floats
 // each (D, then LSE*log2(e)), every region 256-byte aligned; in the dS mode a
@@ -135,6 +136,12 @@ hipError_t launch_bwd_rowdot(const BwdArgs& a);
 hipError_t launch_bwd_dkdv(const BwdArgs& a);
 hipError_t launch_bwd_dq(const BwdArgs& a);  // dQ from stored dS when a.ds is set
 hipError_t launch_bwd(const BwdArgs& a);
+// The forms that launch_bwd takes: keys per dK/dV workgroup, its whole key
+// blocks and those split over two workgroups; waves per dQ workgroup.
+struct BwdForms {
+  int dkdv_keys, dkdv_whole, dkdv_split, dq_waves;
+};
+BwdForms bwd_forms(const BwdArgs& a);
 bool dkdv_one_sum(int Nq);  // every key block sums its query tiles as one sum (never as two added in memory)
 hipError_t launch_merge(const MergeArgs& a);
 

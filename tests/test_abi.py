@@ -434,6 +434,39 @@ def test_bwd_train_output_type_of_dk_and_dv_by_query_count():
     assert kv16(0) == 0 and kv16(-5) == 0
 
 
+# ------------------------------------------------------------ launch forms
+
+
+@pytest.mark.parametrize("flags", [0, 2])
+@pytest.mark.parametrize("d", [8, 64, 72, 88, 128, 160])
+def test_forms_without_a_device_are_the_full_chips(d, flags):
+    # where the runtime can tell nothing about the device, no form made for a
+    # grid that leaves CUs idle may run: large grids would be slower for it
+    import torch
+
+    if torch.cuda.is_available():
+        pytest.skip("needs a machine without a GPU")
+    from paper_2405_15780_amd.binding import launch_forms
+
+    keys = 128 if flags or d > 80 else 256 if d <= 64 else 192
+    for B, H, N in ((1, 1, 1), (1, 2, 188416), (16, 16, 1024), (1, 3, 16321)):
+        f = launch_forms(B, H, N, N, d, flags)
+        blocks = B * H * ((N + keys - 1) // keys)
+        assert (f.fwd_waves, f.dq_waves, f.dkdv_keys, f.dkdv_whole, f.dkdv_split) == (8, 8, keys, blocks, 0), (d, N)
+
+
+def test_launch_forms_reject_bad_arguments():
+    from paper_2405_15780_amd.binding import Forms
+
+    def forms(B=1, H=1, Nq=8, Nk=8, d=64, flags=0, out=ctypes.byref(Forms())):
+        return lib().vitattn_launch_forms(B, H, Nq, Nk, d, flags, out)
+
+    assert forms() == 0
+    for kw, expected in ((dict(B=0), E_INVAL), (dict(Nk=0), E_INVAL), (dict(d=100), E_UNSUP), (dict(flags=4), E_INVAL),
+                         (dict(B=65536, H=65536), E_INVAL), (dict(out=None), E_INVAL)):
+        assert forms(**kw) == expected, kw
+
+
 # ------------------------------------------------------------ dS mode
 
 
