@@ -51,10 +51,10 @@
  *    gives the bits of H single-head calls, whatever the grid or the CU
  *    count. The only atomics are in the dK/dV stage: when its last round of
  *    key-block workgroups would be at most half full, and there are 256 query
- *    tiles of 64 or more, those key blocks are split over two workgroups (one
- *    per half of the query tiles) that add into dK and dV rows zeroed first by
- *    the same call; two fp32 adds onto zero give the same bits in either
- *    order. With that many query tiles every key block, split or not, sums
+ *    tiles of 64 or more, those key blocks may be split over two workgroups
+ *    (one per half of the query tiles) that add into dK and dV rows zeroed
+ *    first by the same call; two fp32 adds onto zero give the same bits in
+ *    either order. With that many query tiles every key block, split or not, sums
  *    them as the same two rounded partial sums (split near the middle query
  *    tile) and adds them, and with fewer as one sum, so splitting changes no
  *    bit. Which blocks split, and how many queries or keys a workgroup takes,
@@ -267,9 +267,10 @@ int vitattn_bwd_train(const void* q, vitattn_strides sq, const void* k, vitattn_
  *   dkdv_keys           : keys per dK/dV workgroup
  *   dkdv_whole          : key blocks (of that many keys) with one workgroup
  *   dkdv_split          : key blocks split over two workgroups
+ *   dkdv_rest64         : workgroups of 64 keys that take the remaining keys
  */
 typedef struct vitattn_forms {
-  int fwd_waves, dq_waves, dkdv_keys, dkdv_whole, dkdv_split;
+  int fwd_waves, dq_waves, dkdv_keys, dkdv_whole, dkdv_split, dkdv_rest64;
 } vitattn_forms;
 int vitattn_launch_forms(int B, int H, int Nq, int Nk, int d, int flags, vitattn_forms* forms);
 

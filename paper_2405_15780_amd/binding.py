@@ -27,7 +27,8 @@ class Strides(ctypes.Structure):
 
 class Forms(ctypes.Structure):
     """vitattn_forms: the kernel forms a call takes."""
-    _fields_ = [(n, ctypes.c_int) for n in ("fwd_waves", "dq_waves", "dkdv_keys", "dkdv_whole", "dkdv_split")]
+    _fields_ = [(n, ctypes.c_int) for n in ("fwd_waves", "dq_waves", "dkdv_keys", "dkdv_whole", "dkdv_split",
+                                              "dkdv_rest64")]
 
 
 _S = Strides

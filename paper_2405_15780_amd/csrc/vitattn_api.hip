@@ -340,7 +340,7 @@ int vitattn_launch_forms(int B, int H, int Nq, int Nk, int d, int flags, vitattn
     f.d = a.d = d;
     if (flags & VITATTN_BWD_STORE_DS) a.ds = reinterpret_cast<uint16_t*>(16);  // selects the mode; never accessed
     const vitattn::BwdForms b = vitattn::bwd_forms(a);
-    *forms = {vitattn::fwd_waves(f), b.dq_waves, b.dkdv_keys, b.dkdv_whole, b.dkdv_split};
+    *forms = {vitattn::fwd_waves(f), b.dq_waves, b.dkdv_keys, b.dkdv_whole, b.dkdv_split, b.dkdv_rest64};
     return VITATTN_OK;
   } catch (...) {
     return VITATTN_E_INTERNAL;

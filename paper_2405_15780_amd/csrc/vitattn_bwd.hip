@@ -93,13 +93,16 @@ constexpr int kDkvBQ = 64;              // queries per streamed tile
 // Query tile at which a key block's two partial sums part, for n tiles; 0: one
 // sum, and the block is never split over two workgroups. The middle, less what
 // makes the first pass a whole number of the kernel's three-tile trips after
-// its first tile. Two sums only serve the split, whose halves add with
-// scattered atomics (~180 us for 128 blocks of 128 keys x 128 columns) to save
-// half a workgroup's time in the last round, 0.9 us per tile: it pays from
-// about 200 tiles on. Below that the second pass, which drains and refills the
-// pipeline, was pure cost (H=256, N=1,024, d=64: 217 -> 153 us with one sum),
-// and where the split was used it was most of the time (H=32, N=1,024, d=64:
-// 223 -> 33 us without it; H=4, N=4,096, d=128: 261 us).
+// its first tile. Two sums only serve the split, but every block pays for them,
+// split or not, as bits must not depend on the grid: the first partial's rows
+// are written, read and written again by all workgroups at once, and the
+// pipeline drains and fills between the passes. From 128 to 255 tiles that took
+// 2-5 % of whole grids' time (H=64, N=8,609, d=160 5,187 us against 4,879; H=5,
+// N=11,285, d=128 578 against 563) and at 16 tiles 40 % (H=256, N=1,024, d=64
+// 217 us against 153). Below 256 tiles the blocks left over go to 64-key
+// workgroups instead (dkdv_mixed). Where a few are left over after one round the
+// split would still be faster, by 0-5 % (stored dS: 0-10 %): H=3, N=11,008,
+// d=128 (258 blocks) 443 us split, 460 so, 506 whole.
 constexpr int kDkvSplitTiles = 256;
 __host__ __device__ constexpr int dkdv_mid(int n) { return n < kDkvSplitTiles ? 0 : n / 2 - (n / 2 + 2) % 3; }
 constexpr int kDkvAhead = 2;            // LDS operand reads this many matrix-core ops ahead (3 measured no better)
@@ -159,16 +162,17 @@ __device__ __forceinline__ void stats_dma(rsrc_t rd, rsrc_t rl, int row0, float*
 //
 // Grid balance: with one workgroup per CU, a grid that is not a whole number
 // of rounds leaves CUs idle in its last round. Workgroups below n_whole each
-// own a key block and every query; the key blocks after them (at most half a
-// round of them) are split into two workgroups each, one per half of the
-// query tiles, which add their dK and dV into rows the launch zeroed first.
+// own a key block (from `first` on) and every query; the key blocks after them
+// (at most half a round of them) are split into two workgroups each, one per
+// half of the query tiles, which add their dK and dV into rows the launch
+// zeroed first.
 template <int D, bool STORE_DS, int KBW, int KPW, int KS = D / 16>
 __global__ __launch_bounds__(128 * KBW, KBW / 2) __attribute__((amdgpu_waves_per_eu(KBW / 2, KBW / 2))) void attn_bwd_dkdv_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const uint16_t* __restrict__ dout, const float* __restrict__ drow, const float* __restrict__ lse2,
     float* __restrict__ dk, float* __restrict__ dv, uint16_t* __restrict__ ds_out, const Map mq, const Map mk,
     const Map mv, const Map mg, const Map mdk, const Map mdv, int H, int dr, int Nq, int Nk, int n_ktiles,
-    int n_whole, float c, float scale, int out16) {
+    int first, int n_whole, float c, float scale, int out16) {
   constexpr int KK = D / 16, NCB = D / 32;
   static_assert(KS >= 1 && KS <= KK, "contraction steps within the tile");
   // operands per phase (each feeding KPW ops): first products (S or dP)
@@ -216,10 +220,10 @@ __global__ __launch_bounds__(128 * KBW, KBW / 2) __attribute__((amdgpu_waves_per
   const bool split = (int)blockIdx.x >= n_whole;
   int work, t0 = 0, t1 = n_qt_real;
   if (!split) {
-    work = xcd_remap(blockIdx.x, n_whole);
+    work = first + xcd_remap(blockIdx.x, n_whole);
   } else {
     const int part = blockIdx.x - n_whole;
-    work = n_whole + (part >> 1);
+    work = first + n_whole + (part >> 1);
     if (part & 1) t0 = dkdv_mid(n_qt_real);
     else t1 = dkdv_mid(n_qt_real);
   }
@@ -279,7 +283,9 @@ __global__ __launch_bounds__(128 * KBW, KBW / 2) __attribute__((amdgpu_waves_per
   // A tile's requests: Q, dO, then the statistics (by waves 0 and 1, which fetch in both modes)
   constexpr int PW = decltype(dma)::PER_WAVE;
   constexpr int NREQ = 2 * PW + 1;
-  static_assert(2 * NREQ <= NA * KPW, "a tile's requests fit its op stream");
+  // one on every odd op, or, where two waves make all of them, on every op
+  constexpr int REQ_STEP = 2 * NREQ <= NA * KPW ? 2 : 1;
+  static_assert(REQ_STEP * NREQ <= NA * KPW, "a tile's requests fit its op stream");
   const int wave_s = __builtin_amdgcn_readfirstlane(wave);
 
   f32x16 acc[KPW][NCB];  // dV^T (role P) or dK^T (role dS) per key block
@@ -487,7 +493,7 @@ __global__ __launch_bounds__(128 * KBW, KBW / 2) __attribute__((amdgpu_waves_per
         acc[kp][j % NCB] = mfma32(aq[a % (AH + 1)], ob[kp][qb][j / NCB], acc[kp][j % NCB]);
         if constexpr (ph == 2) valu(kp, 1, j, P2);
       }
-      if constexpr (i % 2 == 1 && i / 2 < NREQ) prefetch(i / 2);
+      if constexpr (i % REQ_STEP == REQ_STEP - 1 && i / REQ_STEP < NREQ) prefetch(i / REQ_STEP);
       sched_fence();
     });
     __builtin_amdgcn_s_setprio(0);
@@ -1146,40 +1152,78 @@ static Resident dkdv_resident() {
 
 // How a dK/dV launch covers its key blocks: `keys` per workgroup, n_kt key
 // blocks per (b, h), the first n_whole of them one workgroup each and n_split
-// more in two halves each. cost: its estimated time, in rounds of the widest
-// form.
+// more in two halves each; the rest, if any, is covered by a second launch of
+// 64-key workgroups, first64 .. first64 + n_rest64 - 1 of n_kt64 per (b, h).
+// cost: its estimated time. No choice changes a bit of the result.
 struct DkdvPlan {
   int keys, n_kt, n_whole, n_split;
   double cost;
+  int n_kt64 = 0, first64 = 0, n_rest64 = 0;
+};
+static const DkdvPlan& cheaper(const DkdvPlan& x, const DkdvPlan& y) { return y.cost < x.cost ? y : x; }
+
+// A form of the kernel, and what a round of its workgroups takes in units of a
+// full round of the widest form: a full one, and a last one of a few
+// workgroups, of one on nearly every CU and from where two share a CU (fewer
+// CUs at work run faster).
+struct DkdvForm {
+  int keys;
+  Resident r;
+  double round, few, most, shared;
+  double last(int left) const {
+    const double x = (double)left / r.cus;
+    return x <= 1. ? few + (most - few) * x * x : shared + (round - shared) * (x - 1.);
+  }
+  bool known() const { return r.workgroups > 0; }
 };
 
-// Whole rounds of resident workgroups, then the last one, alone on its CUs or
-// two to a CU, or, at most half full, split in two halves of the query range
-// (where the key blocks take two sums). one, two: a round's time with one and
-// with two workgroups per CU. Without the device's figures nothing is split
-// and the widest form wins.
-static DkdvPlan dkdv_form(const BwdArgs& a, int keys, const Resident& r, double one, double two) {
-  const int n_kt = (a.Nk + keys - 1) / keys, n = a.BH * n_kt;
-  if (r.workgroups <= 0) return {keys, n_kt, n, 0, 1. / keys};
-  const int rounds = n / r.workgroups, left = n - rounds * r.workgroups;
+// One form for all key blocks. A last round at most half full is split in two
+// halves of the query range (where the key blocks take two sums): half the
+// time of twice the workgroups, and the halves' atomics, which weigh more
+// where all workgroups reach them at once. Without the device's figures
+// nothing is split and the widest form wins.
+static DkdvPlan dkdv_alike(const BwdArgs& a, const DkdvForm& f) {
+  const int n_kt = (a.Nk + f.keys - 1) / f.keys, n = a.BH * n_kt;
+  if (!f.known()) return {f.keys, n_kt, n, 0, 1. / f.keys};
+  const int rounds = (n - 1) / f.r.workgroups, left = n - rounds * f.r.workgroups;
   const int n_qt = (a.Nq + kDkvBQ - 1) / kDkvBQ;
-  const double full = r.workgroups > r.cus ? two : one;
-  double last = left == 0 ? 0. : left <= r.cus ? one : full;
-  const bool split = left > 0 && 2 * left <= r.workgroups && dkdv_mid(n_qt) > 0;
-  if (split) last = 0.5 * last + 0.8 * left / n_qt * keys * tile_width(a.d) / (128. * 128.);  // the halves' atomics
-  return {keys, n_kt, split ? n - left : n, split ? left : 0, rounds * full + last};
+  if (2 * left > f.r.workgroups || dkdv_mid(n_qt) == 0) return {f.keys, n_kt, n, 0, rounds * f.round + f.last(left)};
+  const double atomics = (rounds > 0 ? 0.25 : 0.55) * left / n_qt * f.keys * tile_width(a.d) / (128. * 128.);
+  return {f.keys, n_kt, n - left, left, rounds * f.round + 0.08 * f.round + 0.5 * f.last(2 * left) + atomics};
 }
-static DkdvPlan cheaper(const DkdvPlan& x, const DkdvPlan& y) { return y.cost < x.cost ? y : x; }
 
+// Whole rounds of `f`, then 64-key workgroups for the key blocks left over
+// (where blocks take one sum, and so cannot be split).
+static DkdvPlan dkdv_mixed(const BwdArgs& a, const DkdvForm& f, const DkdvForm& f64) {
+  const int n_kt = (a.Nk + f.keys - 1) / f.keys, n = a.BH * n_kt;
+  DkdvPlan p = {f.keys, n_kt, n, 0, 1e30};
+  const int n_qt = (a.Nq + kDkvBQ - 1) / kDkvBQ;
+  if (!f.known() || !f64.known() || n % f.r.workgroups == 0 || dkdv_mid(n_qt) > 0) return p;
+  p.n_whole = n - n % f.r.workgroups;
+  p.n_kt64 = a.ds != nullptr ? ds_key_blocks(a.Nk) / 2 : (a.Nk + 63) / 64;  // (all stored dS blocks are written)
+  p.first64 = p.n_whole / n_kt * p.n_kt64 + p.n_whole % n_kt * (f.keys / 64);
+  p.n_rest64 = a.BH * p.n_kt64 - p.first64;
+  const int rounds = (p.n_rest64 - 1) / f64.r.workgroups, left = p.n_rest64 - rounds * f64.r.workgroups;
+  p.cost = rounds * f64.round + f64.last(left);
+  // the second launch waits for the slowest workgroup of the first
+  if (p.n_whole > 0) p.cost += p.n_whole / f.r.workgroups * (1.015 * f.round) + 0.02;
+  return p;
+}
+
+template <int D, bool STORE_DS, int KBW, int KPW, int KS>
+static void dkdv_kernel(const BwdArgs& a, int n_kt, int first, int n_whole, int n_split) {
+  hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, STORE_DS, KBW, KPW, KS>), dim3(n_whole + 2 * n_split), dim3(128 * KBW),
+                     0, a.stream, a.q, a.k, a.v, a.dout, a.drow, a.lse2, a.dk, a.dv, a.ds, a.mq, a.mk, a.mv, a.mg,
+                     a.mdk, a.mdv, a.H, a.d, a.Nq, a.Nk, n_kt, first, n_whole, a.scale * kLog2e, a.scale,
+                     a.kv16 ? 1 : 0);
+}
 template <int D, bool STORE_DS, int KBW, int KPW, int KS>
 static hipError_t dkdv_launch(const BwdArgs& a, const DkdvPlan& p) {
   if (p.n_split > 0)
     hipLaunchKernelGGL(zero_key_blocks_kernel, dim3(2 * p.n_split), dim3(256), 0, a.stream, a.dk, a.dv, a.mdk, a.mdv,
                        a.H, a.d, a.Nk, p.n_kt, p.n_whole, p.keys);
-  hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, STORE_DS, KBW, KPW, KS>), dim3(p.n_whole + 2 * p.n_split),
-                     dim3(128 * KBW), 0, a.stream, a.q, a.k, a.v, a.dout, a.drow, a.lse2, a.dk, a.dv, a.ds, a.mq, a.mk,
-                     a.mv, a.mg, a.mdk, a.mdv, a.H, a.d, a.Nq, a.Nk, p.n_kt, p.n_whole, a.scale * kLog2e, a.scale,
-                     a.kv16 ? 1 : 0);
+  if (p.n_whole + p.n_split > 0) dkdv_kernel<D, STORE_DS, KBW, KPW, KS>(a, p.n_kt, 0, p.n_whole, p.n_split);
+  if (p.n_rest64 > 0) dkdv_kernel<D, STORE_DS, 2, 1, KS>(a, p.n_kt64, p.first64, p.n_rest64, 0);
   return hipGetLastError();
 }
 
@@ -1192,27 +1236,39 @@ static hipError_t dkdv_launch(const BwdArgs& a, const DkdvPlan& p) {
 // SIMD only, which measured 5 % slower at d=128 and no faster at d=96. In the
 // 96-wide tile a head dim up to 80 contracts S and dP over five 16-column
 // steps instead of six, and the recompute mode then fits three waves per SIMD
-// (168 VGPRs): six pairs, 192 keys per workgroup, 4-5 % faster at d=72 on large grids, with
-// the same bits. The dS mode keeps four pairs of one-block waves (its stored
-// dS blocks are laid out per 128 keys).
+// (168 VGPRs): six pairs, 192 keys per workgroup, 4-5 % faster at d=72 on large
+// grids, with the same bits. The dS mode keeps four pairs of one-block waves
+// (its stored dS blocks are laid out per wave of one block).
 // Narrower forms (fewer keys per workgroup, the same ops per key block) run
-// where the widest leaves CUs idle, by the shorter estimated time. A round of
-// them against one of the widest, measured at N = 4,096 .. 16,384: d <= 64
-// four one-block pairs 0.59, two pairs 0.40 alone on a CU and 0.61 two to a
-// CU; d <= 80 four pairs 0.79, two pairs 0.52; else two pairs 0.62-0.67.
-// H=2, N=8,191, d=128: 310 -> 157 us; H=1, N=4,096, d=64: 99 -> 51 us.
+// where the widest leaves CUs idle, on the whole grid or behind the widest
+// form's whole rounds, by the shortest estimated time. The figures are fitted
+// to the launches' times at N = 900 .. 60,000 (1,100 shapes; the choice took
+// 0.1-0.2 % longer than the best one on average). Last rounds, whole and by
+// 64-key workgroups: H=3, N=11,008, d=128 (258 blocks, 256 CUs) 506 and 460 us,
+// stored dS 520 and 482; H=3, N=15,000 (354 blocks) 686 and 631, stored dS 728
+// and 697; H=6, N=7,287, d=160 443 and 388, stored dS 430 and 395. Whole grids:
+// H=2, N=8,191, d=128 310 -> 157 us; H=1, N=4,096, d=64 99 -> 51 us; stored dS
+// H=1, N=2,048, d=160 58 -> 46.
 template <int D, int KS>
 static DkdvPlan dkdv_plan(const BwdArgs& a) {
-  if (a.ds != nullptr) return dkdv_form(a, 128, dkdv_resident<D, true, 4, 1, KS>(), 1., 1.);
+  if (a.ds != nullptr) {
+    const DkdvForm wide = {128, dkdv_resident<D, true, 4, 1, KS>(), 1., 0.5, 1., 1.};
+    const Resident r = dkdv_resident<D, true, 2, 1, KS>();
+    const DkdvForm two = D == 64 ? DkdvForm{64, r, 1.05, 0.42, 0.48, 0.72} : DkdvForm{64, r, 0.64, 0.43, 0.53, 0.64};
+    return cheaper(dkdv_alike(a, wide), dkdv_mixed(a, wide, two));
+  }
   const Resident r4 = dkdv_resident<D, false, 4, 1, KS>(), r2 = dkdv_resident<D, false, 2, 1, KS>();
-  if constexpr (D == 64) {
-    const DkdvPlan wide = dkdv_form(a, 256, dkdv_resident<D, false, 4, 2, KS>(), 1., 1.);
-    return cheaper(cheaper(wide, dkdv_form(a, 128, r4, 0.59, 0.59)), dkdv_form(a, 64, r2, 0.4, 0.61));
-  } else if constexpr (KS == 5) {
-    const DkdvPlan wide = dkdv_form(a, 192, dkdv_resident<D, false, 6, 1, KS>(), 1., 1.);
-    return cheaper(cheaper(wide, dkdv_form(a, 128, r4, 0.79, 0.79)), dkdv_form(a, 64, r2, 0.52, 0.79));
+  if constexpr (D == 64 || KS == 5) {
+    const DkdvForm wide = D == 64 ? DkdvForm{256, dkdv_resident<64, false, 4, 2, 4>(), 1., 0.66, 1., 1.}
+                                  : DkdvForm{192, dkdv_resident<96, false, 6, 1, 5>(), 1., 0.66, 1., 1.};
+    const DkdvForm four = D == 64 ? DkdvForm{128, r4, 0.58, 0.44, 0.58, 0.58} : DkdvForm{128, r4, 0.72, 0.54, 0.72, 0.72};
+    const DkdvForm two = D == 64 ? DkdvForm{64, r2, 0.61, 0.35, 0.37, 0.51} : DkdvForm{64, r2, 0.52, 0.43, 0.52, 0.52};
+    return cheaper(cheaper(dkdv_alike(a, wide), dkdv_mixed(a, wide, two)),
+                   cheaper(dkdv_alike(a, four), dkdv_alike(a, two)));
   } else {
-    return cheaper(dkdv_form(a, 128, r4, 1., 1.), dkdv_form(a, 64, r2, 0.65, 1.));
+    const DkdvForm wide = {128, r4, 1., 0.66, 1., 1.};
+    const DkdvForm two = {64, r2, 0.63, D == 160 ? 0.54 : 0.5, 0.63, 0.63};
+    return cheaper(cheaper(dkdv_alike(a, wide), dkdv_mixed(a, wide, two)), dkdv_alike(a, two));
   }
 }
 template <int D, int KS>
@@ -1231,7 +1287,7 @@ static hipError_t dkdv_d(const BwdArgs& a) {
       const uint16_t* __restrict__, const uint16_t* __restrict__, const uint16_t* __restrict__,               \
       const uint16_t* __restrict__, const float* __restrict__, const float* __restrict__, float* __restrict__, \
       float* __restrict__, uint16_t* __restrict__, const Map, const Map, const Map, const Map, const Map,      \
-      const Map, int, int, int, int, int, int, float, float, int);
+      const Map, int, int, int, int, int, int, int, float, float, int);
 VITATTN_DKDV_INSTANTIATE(128, false, 4, 1, 8)
 VITATTN_DKDV_INSTANTIATE(64, false, 4, 2, 4)
 VITATTN_DKDV_INSTANTIATE(64, false, 4, 1, 4)
@@ -1249,6 +1305,11 @@ VITATTN_DKDV_INSTANTIATE(64, true, 4, 1, 4)
 VITATTN_DKDV_INSTANTIATE(96, true, 4, 1, 6)
 VITATTN_DKDV_INSTANTIATE(96, true, 4, 1, 5)
 VITATTN_DKDV_INSTANTIATE(160, true, 4, 1, 10)
+VITATTN_DKDV_INSTANTIATE(128, true, 2, 1, 8)
+VITATTN_DKDV_INSTANTIATE(64, true, 2, 1, 4)
+VITATTN_DKDV_INSTANTIATE(96, true, 2, 1, 6)
+VITATTN_DKDV_INSTANTIATE(96, true, 2, 1, 5)
+VITATTN_DKDV_INSTANTIATE(160, true, 2, 1, 10)
 #undef VITATTN_DKDV_INSTANTIATE
 
 template <int D, int NW, int RING>
@@ -1393,7 +1454,7 @@ bool dkdv_one_sum(int Nq) { return dkdv_mid((Nq + kDkvBQ - 1) / kDkvBQ) == 0; }
 
 BwdForms bwd_forms(const BwdArgs& a) {
   const DkdvPlan p = dkdv_plan_of(a);
-  return {p.keys, p.n_whole, p.n_split, dq_waves_of(a)};
+  return {p.keys, p.n_whole, p.n_split, p.n_rest64, dq_waves_of(a)};
 }
 
 hipError_t launch_bwd(const BwdArgs& a) {

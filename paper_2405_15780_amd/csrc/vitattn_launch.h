@@ -122,8 +122,8 @@ int fwd_waves(const FwdArgs& a);  // waves per workgroup of the forward that lau
 // Workspace layout of the backward pass: two fp32 regions of region_floats
 // each (D, then LSE*log2(e)), every region 256-byte aligned; in the dS mode a
 // third region holds the dS blocks: 2 KB per 32 keys x 32 queries of every
-// head, key blocks rounded up to the dK/dV kernel's 128 keys and query blocks
-// to its 64-query tiles.
+// head, key blocks rounded up to the dK/dV kernel's 128 keys (its 64-key form
+// covers as many) and query blocks to its 64-query tiles.
 inline size_t bwd_region_floats(long long rows) { return (size_t)((rows + 63) / 64) * 64; }
 inline int ds_key_blocks(int Nk) { return (Nk + 127) / 128 * 4; }
 inline int ds_query_blocks(int Nq) { return (Nq + 63) / 64 * 2; }
@@ -137,9 +137,10 @@ hipError_t launch_bwd_dkdv(const BwdArgs& a);
 hipError_t launch_bwd_dq(const BwdArgs& a);  // dQ from stored dS when a.ds is set
 hipError_t launch_bwd(const BwdArgs& a);
 // The forms that launch_bwd takes: keys per dK/dV workgroup, its whole key
-// blocks and those split over two workgroups; waves per dQ workgroup.
+// blocks and those split over two workgroups, the 64-key workgroups launched
+// behind them; waves per dQ workgroup.
 struct BwdForms {
-  int dkdv_keys, dkdv_whole, dkdv_split, dq_waves;
+  int dkdv_keys, dkdv_whole, dkdv_split, dkdv_rest64, dq_waves;
 };
 BwdForms bwd_forms(const BwdArgs& a);
 bool dkdv_one_sum(int Nq);  // every key block sums its query tiles as one sum (never as two added in memory)

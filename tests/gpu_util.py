@@ -18,6 +18,19 @@ def torch():
     return t
 
 
+def cus():
+    """Compute units of the device (the launch forms below are stated for 256)."""
+    return torch().cuda.get_device_properties(0).multi_processor_count
+
+
+def forms(B, H, Nq, Nk, d, store_ds=False):
+    """The kernel forms that calls of these sizes take on this device."""
+    from paper_2405_15780_amd.binding import launch_forms
+
+    torch().cuda.init()
+    return launch_forms(B, H, Nq, Nk, d, 2 if store_ds else 0)
+
+
 def to_device(bits):
     t = torch()
     return t.from_numpy(np.ascontiguousarray(bits).view(np.int16)).view(t.bfloat16).cuda()

@@ -452,7 +452,8 @@ def test_forms_without_a_device_are_the_full_chips(d, flags):
     for B, H, N in ((1, 1, 1), (1, 2, 188416), (16, 16, 1024), (1, 3, 16321)):
         f = launch_forms(B, H, N, N, d, flags)
         blocks = B * H * ((N + keys - 1) // keys)
-        assert (f.fwd_waves, f.dq_waves, f.dkdv_keys, f.dkdv_whole, f.dkdv_split) == (8, 8, keys, blocks, 0), (d, N)
+        assert (f.fwd_waves, f.dq_waves, f.dkdv_keys, f.dkdv_whole) == (8, 8, keys, blocks), (d, N)
+        assert f.dkdv_split == f.dkdv_rest64 == 0, (d, N)
 
 
 def test_launch_forms_reject_bad_arguments():
