@@ -188,7 +188,7 @@ __global__ __launch_bounds__(256) void attn_agg_fwd_kernel(const uint16_t* __res
 // paper's C = 92 at d = 64) that is a single group of chunks. Each lane
 // accumulates ds_c k_c over the rows it holds, and the rows of a chunk are
 // summed once at the end.
-template <int D, int G>
+template <int D, int G, bool ROWS>
 __global__ __launch_bounds__(256) void attn_agg_bwd_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const float* __restrict__ o, const uint16_t* __restrict__ dout, const float* __restrict__ lse,
@@ -250,14 +250,24 @@ __global__ __launch_bounds__(256) void attn_agg_bwd_kernel(
         const float p = ok[u] ? exp2f(s * c2 - l2) : 0.f;
         const float ds = ok[u] ? p * (dp - Dm) : 0.f;
         const float f = scale * ds;
+        if constexpr (ROWS) {
+          if (ok[u]) {
+            float dkx[8], dvx[8];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          const int row = 256 / D * j + srow;
-          const float fr = __shfl(f, row * LPR), pr = __shfl(p, row * LPR);
-          if ((t0 + u) * RPC + row < C) {
-            const size_t at = sbase + (size_t)(t0 + u) * 512 + 256 * j;
-            store4_stream(dk + at, fr * sq[0], fr * sq[1], fr * sq[2], fr * sq[3]);
-            store4_stream(dv + at, pr * sg[0], pr * sg[1], pr * sg[2], pr * sg[3]);
+            for (int e = 0; e < 8; ++e) dkx[e] = f * qv[e], dvx[e] = p * g[e];
+            store8(dk + base + (size_t)(t0 + u) * 512, dkx);
+            store8(dv + base + (size_t)(t0 + u) * 512, dvx);
+          }
+        } else {
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            const int row = 256 / D * j + srow;
+            const float fr = __shfl(f, row * LPR), pr = __shfl(p, row * LPR);
+            if ((t0 + u) * RPC + row < C) {
+              const size_t at = sbase + (size_t)(t0 + u) * 512 + 256 * j;
+              store4_stream(dk + at, fr * sq[0], fr * sq[1], fr * sq[2], fr * sq[3]);
+              store4_stream(dv + at, pr * sg[0], pr * sg[1], pr * sg[2], pr * sg[3]);
+            }
           }
         }
 #pragma unroll
@@ -306,14 +316,15 @@ __global__ __launch_bounds__(1024) void attn_agg_dq_kernel(const float* __restri
   template __global__ void attn_agg_fwd_kernel<D, G>(const uint16_t* __restrict__, const uint16_t* __restrict__, \
                                                      const uint16_t* __restrict__, float* __restrict__,       \
                                                      float* __restrict__, int, int, int, float);
-#define VITATTN_AGG_BWD_INSTANTIATE(D, G)                                                                      \
-  template __global__ void attn_agg_bwd_kernel<D, G>(                                                         \
+#define VITATTN_AGG_BWD_INSTANTIATE(D, G, ROWS)                                                                \
+  template __global__ void attn_agg_bwd_kernel<D, G, ROWS>(                                                         \
       const uint16_t* __restrict__, const uint16_t* __restrict__, const uint16_t* __restrict__,               \
       const float* __restrict__, const uint16_t* __restrict__, const float* __restrict__, float* __restrict__, \
       float* __restrict__, float* __restrict__, int, int, int, float, float);
 // group sizes of the two passes (see agg_group)
 #define VITATTN_AGG_FWD_GROUPS(X, D) X(D, 1) X(D, 2) X(D, 3) X(D, 4) X(D, 6) X(D, 8) X(D, 10) X(D, 12)
-#define VITATTN_AGG_BWD_GROUPS(X, D) X(D, 1) X(D, 2) X(D, 3) X(D, 4) X(D, 12)
+#define VITATTN_AGG_BWD_GROUPS(X, D) \
+  X(D, 1, false) X(D, 2, false) X(D, 3, false) X(D, 4, false) X(D, 12, false) X(D, 12, true)
 VITATTN_AGG_FWD_GROUPS(VITATTN_AGG_FWD_INSTANTIATE, 64)
 VITATTN_AGG_FWD_GROUPS(VITATTN_AGG_FWD_INSTANTIATE, 128)
 VITATTN_AGG_BWD_GROUPS(VITATTN_AGG_BWD_INSTANTIATE, 64)
@@ -333,10 +344,26 @@ int agg_partials(int M) { return (M + 3) / 4; }
 // from five chunks on: with smaller ones more waves are in flight and their
 // stores come between other waves' loads (M=8,192, H=16, C=33: 605 us in
 // groups of 12, 651 in groups of 6, both before the stores were streamed).
+// The size follows C and d alone, so that a patch's bits do not depend on M.
+// At 7-8 and 13-16 chunks that has two sides, against groups of 12 (H=16,
+// d=64): C=99 M=600 40 -> 38 us, M=5,000 337 -> 350; C=64 M=200 12.8 -> 11.7,
+// M=5,000 221 -> 227.
 static int agg_group(int C, int d) {
   const int chunks = (C + 512 / d - 1) / (512 / d);
   const int groups = (chunks + kAggChunkGroup - 1) / kAggChunkGroup;
   return (chunks + groups - 1) / groups;
+}
+
+// Whether the backward's lanes store the eight columns they load, through the
+// caches, instead of the four that make consecutive streamed stores. Patches
+// of more than one group of chunks load again after their first stores, and in
+// calls of more than about 450 MB each of K and V that took 1-3 % longer with
+// the streamed stores (H=16: M=4,000, C=110, d=64 1,061 us against 1,035;
+// M=2,000, C=65, d=128 634 against 620); below that they are faster (M=600,
+// C=99, d=64 118 against 157). Same products, same bits.
+static bool agg_bwd_rows(const AggArgs& a) {
+  const int chunks = (a.C + 512 / a.d - 1) / (512 / a.d);
+  return chunks > kAggChunkGroup && (long long)a.M * a.H * chunks > 440000;
 }
 
 template <int D, int G>
@@ -347,10 +374,10 @@ static hipError_t agg_fwd_g(const AggArgs& a) {
   return hipGetLastError();
 }
 
-template <int D, int G>
+template <int D, int G, bool ROWS>
 static hipError_t agg_bwd_g(const AggArgs& a) {
   const int parts = agg_partials(a.M);
-  hipLaunchKernelGGL((attn_agg_bwd_kernel<D, G>), dim3((unsigned)(parts * a.H)), dim3(256), 0, a.stream, a.q, a.k,
+  hipLaunchKernelGGL((attn_agg_bwd_kernel<D, G, ROWS>), dim3((unsigned)(parts * a.H)), dim3(256), 0, a.stream, a.q, a.k,
                      a.v, a.o, a.dout, a.lse, a.dk, a.dv, a.partial, a.M, a.H, a.C, a.scale * kLog2e, a.scale);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -372,8 +399,9 @@ static hipError_t agg_fwd_d(const AggArgs& a) {
 template <int D>
 static hipError_t agg_bwd_d(const AggArgs& a) {
   const int g = agg_group(a.C, D);
-#define VITATTN_AGG_LAUNCH(D_, G) \
-  if (g <= G) return agg_bwd_g<D_, G>(a);
+  const bool rows = agg_bwd_rows(a);
+#define VITATTN_AGG_LAUNCH(D_, G, ROWS) \
+  if (g <= G && rows == ROWS) return agg_bwd_g<D_, G, ROWS>(a);
   VITATTN_AGG_BWD_GROUPS(VITATTN_AGG_LAUNCH, D)
 #undef VITATTN_AGG_LAUNCH
   return hipErrorInvalidValue;

@@ -6,13 +6,34 @@ import pytest
 
 from oracle import aggregation as agg
 import workloads
-from gpu_util import rel_l2, to_device
+from gpu_util import rel_l2, to_device, torch
 
 pytestmark = pytest.mark.gpu
 
 
 def np64(t):
     return t.detach().double().cpu().numpy()
+
+
+@pytest.mark.parametrize("C,d", [(101, 64), (128, 64), (49, 128), (66, 128)])
+def test_large_calls_store_the_bits_of_small_ones(C, d):
+    # past 440,000 chunks of more than one group the backward stores whole rows of its lanes
+    import paper_2405_15780_amd as va
+
+    t = torch()
+    H, chunks = 16, -(-C // (512 // d))
+    M = 440000 // (H * chunks) + 8
+    print(f"case aggregation large call M={M} H={H} C={C} d={d}", flush=True)
+    g = t.Generator(device="cuda").manual_seed(7300 + C)
+    q, k, v, do = (t.randn(s, generator=g, device="cuda").bfloat16()
+                   for s in ((H, d), (M, H, C, d), (M, H, C, d), (M, H, d)))
+    o, lse = va.agg_fwd(q, k, v)
+    _, dk, dv = va.agg_bwd(q, k, v, o, lse, do)
+    for m in (slice(0, M // 2), slice(M // 2, M)):
+        o2, lse2 = va.agg_fwd(q, k[m], v[m])
+        _, dk2, dv2 = va.agg_bwd(q, k[m], v[m], o2, lse2, do[m])
+        for name, a, b in (("o", o, o2), ("lse", lse, lse2), ("dk", dk, dk2), ("dv", dv, dv2)):
+            assert t.equal(a[m], b), name
 
 
 @pytest.mark.parametrize("d", [64, 128])
