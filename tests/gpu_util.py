@@ -36,6 +36,31 @@ def to_device(bits):
     return t.from_numpy(np.ascontiguousarray(bits).view(np.int16)).view(t.bfloat16).cuda()
 
 
+def random_qkvg(B, H, Nq, Nk, d, seed):
+    """Random bf16 q, k, v and dout on the device (Nq queries, Nk keys)."""
+    t = torch()
+    g = t.Generator(device="cuda").manual_seed(seed)
+    return [t.randn((B, H, n, d), generator=g, device="cuda").bfloat16() for n in (Nq, Nk, Nk, Nq)]
+
+
+def bits(x):
+    """The bf16 bit patterns of a device tensor, as the oracle takes them."""
+    return x.contiguous().view(torch().int16).cpu().numpy().view(np.uint16)
+
+
+def run_device(q, k, v, g, scale, store_ds=False):
+    """Forward and backward of device tensors through the binding."""
+    import paper_2405_15780_amd as va
+
+    t = torch()
+    o, lse = va.fwd(q, k, v, scale)
+    dq, dk, dv = va.bwd(q, k, v, o, lse, g, scale, store_ds=store_ds)
+    t.cuda.synchronize()
+    if store_ds:
+        t.cuda.empty_cache()
+    return {"o": o, "lse": lse, "dq": dq, "dk": dk, "dv": dv}
+
+
 def run_hip(x, scale, backward=True, store_ds=False):
     """Forward (and backward) through the binding; store_ds selects the
     backward's dS mode (dQ from stored dS), whose workspace is freed again."""

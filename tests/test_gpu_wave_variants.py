@@ -1,20 +1,20 @@
 """At the narrowest tile (head dims up to 64) the forward and dQ kernels
-choose between 8- and 12-wave workgroups from the grid size, and each dK/dV
-wave holds two 32-key blocks (256 keys per workgroup); in the 96-wide tile
-with d <= 80 the dQ kernel makes the same choice and dK/dV runs six pairs of
-waves (192 keys). B=1, H=6, N=22,001 makes the six-head call take the
-12-wave dQ (and at d <= 64 forward) on a 256-CU part (two rounds of
-384-query workgroups instead of three of 256) while each single-head call
-takes the 8-wave ones; dK/dV splits 4 of its 516 key blocks at d <= 64 (none
-of 690 at d = 72) where a single-head call splits all 86 (115). Every
-output must be bitwise equal between the two, and sampled query and key
-rows must match the fp64 oracle."""
+choose between 4-, 8- and 12-wave workgroups from the grid size, and each
+dK/dV wave holds two 32-key blocks (256 keys per workgroup); in the 96-wide
+tile with d <= 80 the dQ kernel makes the same choice and dK/dV runs six pairs
+of waves (192 keys). B=1, H=4, N=24,545 makes the four-head call take the
+12-wave dQ (and at d <= 64 forward) on a 256-CU part (one round of 384-query
+workgroups instead of one and a half of 256) while each single-head call takes
+the 4-wave ones; dK/dV splits 128 of its 384 key blocks at d <= 64 (none of
+512 at d = 72) and takes another form for a single head. Every output must be
+bitwise equal between the two, and sampled query and key rows must match the
+fp64 oracle."""
 import numpy as np
 import pytest
 
 import oracle
 import workloads
-from gpu_util import assert_close, run_hip, torch
+from gpu_util import assert_close, cus, forms, run_hip, torch
 
 pytestmark = pytest.mark.gpu
 
@@ -23,11 +23,22 @@ def np64(t):
     return t.detach().double().cpu().numpy()
 
 
+def check_forms(H, N, d):
+    if cus() != 256:
+        return
+    f, one = forms(1, H, N, N, d), forms(1, 1, N, N, d)
+    assert (f.fwd_waves, f.dq_waves) == (12 if d <= 64 else 4, 12)
+    assert (one.fwd_waves, one.dq_waves) == (4, 4)
+    assert (f.dkdv_keys, f.dkdv_whole, f.dkdv_split) == ((256, 256, 128) if d <= 64 else (192, 512, 0))
+    assert one.dkdv_keys < f.dkdv_keys
+
+
 @pytest.mark.parametrize("d", [56, 64, 72])
 def test_twelve_wave_grid_matches_single_heads_and_oracle(d):
     t = torch()
-    B, H, N = 1, 6, 22001
+    B, H, N = 1, 4, 24545
     print(f"case wave variants B={B} H={H} N={N} d={d}", flush=True)
+    check_forms(H, N, d)
     x = workloads.make_small_inputs(B, H, N, d, seed=9900 + d)
     scale = 1.0 / np.sqrt(d)
     full = run_hip(x, scale)
@@ -42,7 +53,7 @@ def test_twelve_wave_grid_matches_single_heads_and_oracle(d):
     sel = tuple(t.from_numpy(rows[:, i]).cuda() for i in range(3))
     got = {n: np64(full[n][sel]) for n in ("o", "lse", "dq")}
     assert_close(got, ref, names=("o", "lse", "dq"), label=f"wave variants d={d} sampled query rows")
-    h = 4
+    h = 3
     lse, D = oracle.row_statistics(x["q"], x["k"], x["v"], x["dout"], scale, 0, h)
     keys = np.sort(rng.choice(N, 64, replace=False))
     dk, dv = oracle.key_rows(x["q"], x["k"], x["v"], x["dout"], scale, 0, h, keys, lse, D)
@@ -58,8 +69,9 @@ def test_twelve_wave_grid_in_the_sequence_major_layout():
     import paper_2405_15780_amd as va
 
     t = torch()
-    B, H, N, d = 1, 6, 22001, 64
+    B, H, N, d = 1, 4, 24545, 64
     print(f"case wave variants sequence-major B={B} H={H} N={N} d={d}", flush=True)
+    check_forms(H, N, d)
     x = workloads.make_small_inputs(B, H, N, d, seed=9990)
     scale = 1.0 / np.sqrt(d)
     dense = run_hip(x, scale)
