@@ -4,16 +4,65 @@ that nothing wrote would turn outputs into NaN. Each case runs through the
 normal library and then through the poisoned one (swapped in for the
 package's library), and every output must be equal bitwise: forward and both
 backward modes over ragged tails, Nq != Nk, every tile width and a
-sequence-major layout, the merge and the channel aggregation."""
+sequence-major layout, the merge and the channel aggregation. The short cases
+take the kernels' narrow forms; FULL fills 256 CUs and takes the wide ones
+(eight waves per workgroup in the forward and dQ, twelve where there are such,
+the widest dK/dV with 64-key workgroups behind it, and split key blocks)."""
 import os
 
 import numpy as np
 import pytest
 
 import workloads
-from gpu_util import to_device, torch
+from gpu_util import cus, forms, random_qkvg, to_device, torch
 
 pytestmark = pytest.mark.gpu
+
+
+# H, Nq, Nk, d and what the recompute mode takes: forward and dQ waves, dK/dV keys, split blocks
+FULL = [(64, 1001, 2501, 64, 8, 8, 256, 0), (64, 1001, 2501, 72, 8, 8, 128, 0), (64, 1001, 2501, 88, 8, 8, 128, 0),
+        (64, 1001, 2501, 128, 8, 8, 128, 0), (64, 1001, 2501, 160, 8, 8, 128, 0), (64, 1530, 2501, 64, 12, 12, 256, 0),
+        (64, 1530, 2501, 72, 4, 12, 128, 0), (9, 200, 11001, 72, 4, 4, 192, 0), (26, 16400, 2500, 64, 4, 8, 256, 4),
+        (52, 16400, 1900, 72, 4, 12, 192, 8), (26, 16400, 1250, 96, 4, 4, 128, 4), (26, 16400, 1250, 128, 4, 8, 128, 4),
+        (26, 16400, 1250, 160, 4, 8, 128, 4)]
+
+
+def test_full_grids_take_the_wide_forms():
+    if cus() != 256:
+        pytest.skip("the shapes are made for 256 CUs")
+    for H, Nq, Nk, d, fwd, dq, keys, split in FULL:
+        f = forms(1, H, Nq, Nk, d)
+        assert (f.fwd_waves, f.dq_waves, f.dkdv_keys, f.dkdv_split) == (fwd, dq, keys, split), (H, Nq, Nk, d)
+        assert f.dkdv_whole >= 256
+
+
+@pytest.mark.parametrize("H,Nq,Nk,d", [c[:4] for c in FULL])
+def test_poisoned_lds_changes_no_output_on_full_grids(H, Nq, Nk, d):
+    import paper_2405_15780_amd as va
+    import paper_2405_15780_amd.binding as b
+    from paper_2405_15780_amd._build import LDS_POISON_LIB_PATH
+
+    t = torch()
+    print(f"case LDS poison full grid H={H} Nq={Nq} Nk={Nk} d={d}", flush=True)
+    q, k, v, g = random_qkvg(1, H, Nq, Nk, d, seed=9300 + d)
+    normal = b.library()
+    libs = (normal, b.open_library(LDS_POISON_LIB_PATH))
+    try:
+        for store_ds in (False, True):
+            ref = None
+            for lib in libs:
+                b._lib = lib
+                o, lse = va.fwd(q, k, v)
+                got = (o, lse) + tuple(va.bwd(q, k, v, o, lse, g, store_ds=store_ds))
+                t.cuda.synchronize()
+                if ref is None:
+                    ref = got
+            for name, x, y in zip(("o", "lse", "dq", "dk", "dv"), ref, got):
+                assert bool(t.isfinite(y).all()), f"{name}: non-finite values with poisoned LDS"
+                assert t.equal(x, y), f"{name} differs when the kernels' LDS starts as NaN (store_ds={store_ds})"
+            t.cuda.empty_cache()
+    finally:
+        b._lib = normal
 
 
 def _outputs():
