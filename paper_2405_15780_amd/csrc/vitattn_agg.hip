@@ -218,9 +218,9 @@ __global__ __launch_bounds__(256) void attn_agg_bwd_kernel(
     // a wave's store 1 KB of consecutive bytes, half a chunk, and fetches the
     // numbers from the row's first lane. Storing the eight columns a lane
     // loads wrote every other 16 bytes per instruction. The stores are
-    // streamed. Forward + backward, M=8,192, H=16, d=64: C=92 2,343 -> 2,303
-    // us, C=33 824 -> 763, C=24 647 -> 578; M=2,000, C=8 66 -> 53 (without
-    // streaming 2,333, 811, 626 and 63). Same products, same bits.
+    // streamed. M=8,192, H=16, d=64: C=92 1,803 -> 1,780 us, C=33 603 -> 567,
+    // C=24 483 -> 434; M=2,000, C=24 125 -> 93, C=8 39.5 -> 36.6; the rows'
+    // consecutive order alone gave a quarter of that. Same products, same bits.
     const int srow = 4 * lane / D, scol = 4 * lane % D;
     const size_t sbase = inst * C * D + 4 * lane;
     float sq[4], sg[4];
@@ -340,7 +340,7 @@ int agg_partials(int M) { return (M + 3) / 4; }
 // that is instantiated. A fixed group of 12 went through its arithmetic for
 // chunks a patch doesn't have and held their registers: M=2,000, H=16, d=64,
 // C=8 (one chunk) forward 37.1 -> 16.9 us, backward 87 -> 39 us; M=8,192, C=24
-// (three) 184 -> 132 us and 495 -> 477 us. The backward takes groups of 12
+// (three) 190 -> 144 us and 503 -> 483 us. The backward takes groups of 12
 // from five chunks on: with smaller ones more waves are in flight and their
 // stores come between other waves' loads (M=8,192, H=16, C=33: 605 us in
 // groups of 12, 651 in groups of 6, both before the stores were streamed).

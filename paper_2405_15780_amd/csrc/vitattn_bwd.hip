@@ -1411,14 +1411,17 @@ static Resident dq_resident() {
 // three waves per SIMD (three to five values spilled, outside the loop but for
 // one operand at D = 96): 12 waves (384 queries) share each K / V tile, 2 %
 // faster per query than 8 (B=4, H=1, N=188,416, d=64: 48.3 -> 47.2 ms; H=2,
-// d=72: 29.4 -> 28.8 ms), but in coarser work items. All compute every dQ row
+// d=72: 29.4 -> 28.8 ms), but in coarser work items. At d <= 64 they count as
+// 4 % faster, as a last round of them that is not full costs less than a whole
+// one: B=1, H=1, N=1,048,576, d=64 (10.7 rounds against 16 of 8 waves) 369.6 ->
+// 360.1 ms; H=16, N=65,536 23.4 -> 22.6 ms (at d=72 27.4 with 12, 26.7 with 8). All compute every dQ row
 // with the same operations in the same order, so the choice changes no bit.
 template <int D, int KS>
 static int dq_waves(const BwdArgs& a) {
   const double c8 = launch_cost(a.BH, a.Nq, a.Nk, 8, dq_resident<D, 8, KS>());
   const double c4 = launch_cost(a.BH, a.Nq, a.Nk, 4, dq_resident<D, 4, KS>());
   if constexpr (KS <= 5) {
-    const double c12 = launch_cost(a.BH, a.Nq, a.Nk, 12, dq_resident<D, 12, KS>()) / 1.02;
+    const double c12 = launch_cost(a.BH, a.Nq, a.Nk, 12, dq_resident<D, 12, KS>()) / (D == 64 ? 1.04 : 1.02);
     if (c12 < c8 && c12 < c4) return 12;
   }
   return c4 < c8 ? 4 : 8;

@@ -62,6 +62,14 @@ def test_twelve_wave_grid_matches_single_heads_and_oracle(d):
                  names=("dk", "dv"), label=f"wave variants d={d} sampled key rows")
 
 
+def test_long_sequences_take_twelve_wave_dq():
+    # many rounds: 384-query workgroups are faster though their last round is counted whole
+    if cus() != 256:
+        pytest.skip("the shapes are made for 256 CUs")
+    for H, N in ((1, 1048576), (16, 65536)):
+        assert forms(1, H, N, N, 64).dq_waves == 12, (H, N)
+
+
 def test_twelve_wave_grid_in_the_sequence_major_layout():
     # the same grid through the strided entry points ([B, N, H, d] operands
     # and outputs, as an all-to-all hands them over): bitwise equal to the
